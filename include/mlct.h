@@ -330,9 +330,8 @@ mlct_status mlct_moments(mlct_ctx* ctx, const mlct_op* op, double a, double b, i
  * Scratch: a fixed device array of MLCT_NOALLOC_SCRATCH_BYTES inside the
  * library, one per GPU, held until the process ends.  A request needs
  * 2 d 64 s bytes (two probe vectors, s = 4 or 8) + 1024 G (S + 1) (moment
- * partials; G workgroups per step, up to 2048; S steps) + 1024 (S + 1) + 64 s
- * per 256-entry chunk of the rows longer than 256 entries, each part rounded
- * up to 256; more than the array holds fails with MLCT_ENOMEM before any work
+ * partials; G workgroups per step, up to 2048; S steps) + 1024 (S + 1), each
+ * part rounded up to 256; more than the array holds fails with MLCT_ENOMEM before any work
  * (about d <= 65,536 rows in FP32 at degree 200, symmetric form).  Every
  * buffer is written
  * before it is read, so nothing needs clearing between calls.  All calls on

@@ -314,20 +314,19 @@ constexpr int kSharedBlocks = 4;
 // ``src.active`` probes of one block and writes their moments mu_0..mu_n
 // (n = degree) into mu_rows (device, row stride ldmu).
 // Device buffers of one CSR probe block: the two vector buffers, the moment
-// partials of every step, the reduced dots and the hub chunk sums.
+// partials of every step and the reduced dots.
 struct CsrBlockBufs {
   void* v0 = nullptr;
   void* v1 = nullptr;
   double* part = nullptr;
   double* dots = nullptr;
-  void* hub = nullptr;
   bool timed = true;  // record kernel timing events (these may allocate)
   int* fsync = nullptr;  // two-step launches: tickets, flags and abort flag (null: single steps)
 };
 
 // Bytes of each buffer for a block of degree ``degree`` in form ``mode``.
 struct CsrBlockSizes {
-  size_t v, part, dots, hub;
+  size_t v, part, dots;
 };
 CsrBlockSizes csr_block_sizes(const mlct_op* op, size_t tsz, int mode, int degree) {
   const int S = (mode == MLCT_DOUBLING) ? (degree + 1) / 2 : degree;
@@ -336,7 +335,6 @@ CsrBlockSizes csr_block_sizes(const mlct_op* op, size_t tsz, int mode, int degre
   z.v = (size_t)op->d * kBlockProbes * tsz;
   z.part = (size_t)2 * plan.ngroups * kBlockProbes * (S + 1) * sizeof(double);
   z.dots = (size_t)(S + 1) * 2 * kBlockProbes * sizeof(double);
-  z.hub = op->csr.hub_n > 0 ? (size_t)op->csr.hub_chunks * kBlockProbes * tsz : 0;
   return z;
 }
 
@@ -439,7 +437,6 @@ mlct_status run_block_csr_in(mlct_ctx* ctx, const mlct_op* op, double alpha, dou
   T* buf[2] = {static_cast<T*>(bb.v0), static_cast<T*>(bb.v1)};
   double* P = bb.part;
   void* dots = bb.dots;
-  void* hub = bb.hub;
   hipStream_t s = ctx->stream;
   HIPCHK(ctx, launch_probe_init<T>(s, buf[0], op->d, src, plan, P));
   const int zdirect = src.entries ? 2 : 1;
@@ -453,11 +450,11 @@ mlct_status run_block_csr_in(mlct_ctx* ctx, const mlct_op* op, double alpha, dou
     const int zmode = (mode == MLCT_DOUBLING || first) ? 0 : zdirect;
     if (bb.timed) {
       LaunchTimer tm(ctx, MLCT_KERNEL_CSR_STEP);
-      HIPCHK(ctx, launch_csr_step<T>(s, op->csr, vk, vm, ca, cb, !first, zmode, src, plan, hub,
+      HIPCHK(ctx, launch_csr_step<T>(s, op->csr, vk, vm, ca, cb, !first, zmode, src, plan,
                                      P + pstep * k));
       tm.done();
     } else {
-      HIPCHK(ctx, launch_csr_step<T>(s, op->csr, vk, vm, ca, cb, !first, zmode, src, plan, hub,
+      HIPCHK(ctx, launch_csr_step<T>(s, op->csr, vk, vm, ca, cb, !first, zmode, src, plan,
                                      P + pstep * k));
     }
   }
@@ -497,7 +494,6 @@ mlct_status run_block_csr(mlct_ctx* ctx, const mlct_op* op, double alpha, double
   CHECK(ws_get(ctx, WS_V1, z.v, &bb.v1));
   CHECK(ws_get(ctx, WS_PART, z.part, &part));
   CHECK(ws_get(ctx, WS_MISC, z.dots, &dots));
-  if (z.hub) CHECK(ws_get(ctx, WS_HUB, z.hub, &bb.hub));
   bb.part = static_cast<double*>(part);
   bb.dots = static_cast<double*>(dots);
   const CsrStepPlan plan = plan_csr(op->d, op->tuned_groups);
@@ -581,16 +577,12 @@ mlct_status run_block_gram_csr(mlct_ctx* ctx, const mlct_op* op, double alpha, d
   const CsrStepPlan plan_r = plan_csr(op->csrx.nrows, op->tuned_groups);
   const size_t vbytes = (size_t)op->d * kBlockProbes * sizeof(T);
   const size_t pstep = (size_t)2 * plan.ngroups * kBlockProbes;
-  void *v0, *v1, *part, *dots, *wb, *hubs = nullptr;
+  void *v0, *v1, *part, *dots, *wb;
   CHECK(ws_get(ctx, WS_V0, vbytes, &v0));
   CHECK(ws_get(ctx, WS_V1, vbytes, &v1));
   CHECK(ws_get(ctx, WS_PART, pstep * (S + 1) * sizeof(double), &part));
   CHECK(ws_get(ctx, WS_MISC, (size_t)(S + 1) * 2 * kBlockProbes * sizeof(double), &dots));
   CHECK(ws_get(ctx, WS_GRAMW, (size_t)op->csrx.nrows * kBlockProbes * sizeof(T), &wb));
-  const size_t hx = (size_t)op->csrx.hub_chunks * kBlockProbes, ht = (size_t)op->csr.hub_chunks * kBlockProbes;
-  if (hx + ht > 0) CHECK(ws_get(ctx, WS_HUB, (hx + ht) * sizeof(T), &hubs));
-  T* hubx = static_cast<T*>(hubs);
-  T* hubt = hubx ? hubx + hx : nullptr;
   T* buf[2] = {static_cast<T*>(v0), static_cast<T*>(v1)};
   T* W = static_cast<T*>(wb);
   double* P = static_cast<double*>(part);
@@ -606,7 +598,7 @@ mlct_status run_block_gram_csr(mlct_ctx* ctx, const mlct_op* op, double alpha, d
     const int zmode = (mode == MLCT_DOUBLING || first) ? 0 : zdirect;
     LaunchTimer tm(ctx, MLCT_KERNEL_GRAM_CSR_STEP);
     HIPCHK(ctx, launch_gram_csr_step<T>(s, op->csrx, op->csr, vk, vm, W, (T)ca, (T)cb, !first,
-                                        zmode, src, plan_r, plan, hubx, hubt, P + pstep * k));
+                                        zmode, src, plan_r, plan, P + pstep * k));
     tm.done();
   }
   HIPCHK(ctx, launch_reduce_partials(s, P, S + 1, 2, plan.ngroups, kBlockProbes,
@@ -796,8 +788,6 @@ mlct_status reserve_block_ws(mlct_ctx* ctx, const mlct_op* op, int prec, int mod
     CHECK(ws_get(ctx, WS_V1, (size_t)op->d * kBlockProbes * tsz, &tmp));
     CHECK(ws_get(ctx, WS_PART, (size_t)2 * plan.ngroups * kBlockProbes * (S + 1) * sizeof(double), &tmp));
     CHECK(ws_get(ctx, WS_MISC, (size_t)(S + 1) * 2 * kBlockProbes * sizeof(double), &tmp));
-    const size_t hubs = (size_t)op->csr.hub_chunks + (op->kind == OP_GRAM_CSR ? op->csrx.hub_chunks : 0);
-    if (hubs > 0) CHECK(ws_get(ctx, WS_HUB, hubs * kBlockProbes * tsz, &tmp));
     if (op->kind == OP_GRAM_CSR)
       CHECK(ws_get(ctx, WS_GRAMW, (size_t)op->csrx.nrows * kBlockProbes * tsz, &tmp));
     return MLCT_OK;
@@ -1329,7 +1319,7 @@ mlct_status mlct_moments_noalloc(mlct_ctx* ctx, const mlct_op* op, double a, dou
   const size_t tsz = prec == MLCT_FP64 ? 8 : 4;
   const CsrBlockSizes z = csr_block_sizes(op, tsz, mode, n);
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t need = 2 * up(z.v) + up(z.part) + up(z.dots) + up(z.hub);
+  const size_t need = 2 * up(z.v) + up(z.part) + up(z.dots);
   if (need > (size_t)MLCT_NOALLOC_SCRATCH_BYTES)
     return fail(ctx, MLCT_ENOMEM,
                 "needs %zu bytes of scratch, more than the fixed %llu (fewer rows or a lower degree)",
@@ -1343,7 +1333,6 @@ mlct_status mlct_moments_noalloc(mlct_ctx* ctx, const mlct_op* op, double a, dou
   bb.v1 = base + up(z.v);
   bb.part = reinterpret_cast<double*>(base + 2 * up(z.v));
   bb.dots = reinterpret_cast<double*>(base + 2 * up(z.v) + up(z.part));
-  bb.hub = z.hub ? base + 2 * up(z.v) + up(z.part) + up(z.dots) : nullptr;
   const double alpha = 2.0 / (b - a), beta = -(a + b) / (b - a);
   const int64_t ldmu = n + 1;
   for (int64_t p0 = 0; p0 < probes->m; p0 += kBlockProbes) {
@@ -2269,7 +2258,7 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     }
     const bool pat = it.op->csr.val == nullptr;
     // row-length class: straight-line gathers up to 4 / 5 / 8 entries, or
-    // 9 = longer rows present (the generic loop)
+    // 9 = longer rows present
     const int mxr = it.op->csr.max_row_nnz;
     const int mz = mxr <= 4 ? 4 : mxr <= 5 ? 5 : mxr <= 8 ? 8 : 9;
     int var = -1;
@@ -2350,6 +2339,8 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     B.ngroups = plan.ngroups;
     B.rows_per_group = plan.rows_per_group;
     B.band = op->csr.band && op->csr.band_groups == plan.ngroups ? op->csr.band : nullptr;
+    B.hubs = HubRows{op->csr.hub_rows, op->csr.hub_c0, op->csr.hub_cs, op->csr.hub_ce,
+                     op->csr.hub_n};
   }
   std::vector<double*> mu(nitems), coef(nitems), qst(nitems);
   for (int i = 0; i < nitems; ++i) {
@@ -2643,7 +2634,7 @@ mlct_status run_block_slq(mlct_ctx* ctx, const mlct_op* op, int k, mlct_func f,
                           double log_scale, ProbeSrc src, double* q_dev) {
   const CsrStepPlan plan = plan_csr(op->d, op->tuned_groups);
   const size_t vbytes = (size_t)op->d * kBlockProbes * sizeof(double);
-  void *w0, *w1, *w, *part, *dots, *hub = nullptr;
+  void *w0, *w1, *w, *part, *dots;
   CHECK(ws_get(ctx, WS_V0, vbytes, &w0));
   CHECK(ws_get(ctx, WS_V1, vbytes, &w1));
   const size_t state_off = (vbytes + 255) & ~(size_t)255;
@@ -2651,8 +2642,6 @@ mlct_status run_block_slq(mlct_ctx* ctx, const mlct_op* op, int k, mlct_func f,
   CHECK(ws_get(ctx, WS_SLQ, scratch_off + (size_t)3 * k * 64 * sizeof(double), &w));
   CHECK(ws_get(ctx, WS_PART, (size_t)2 * plan.ngroups * kBlockProbes * sizeof(double), &part));
   CHECK(ws_get(ctx, WS_MISC, (size_t)2 * kBlockProbes * sizeof(double), &dots));
-  if (op->csr.hub_n > 0)
-    CHECK(ws_get(ctx, WS_HUB, (size_t)op->csr.hub_chunks * kBlockProbes * sizeof(double), &hub));
   double* W0 = static_cast<double*>(w0);
   double* W1 = static_cast<double*>(w1);
   double* U = static_cast<double*>(w);
@@ -2667,7 +2656,7 @@ mlct_status run_block_slq(mlct_ctx* ctx, const mlct_op* op, int k, mlct_func f,
   HIPCHK(ctx, launch_slq_init(s, D, k, st));
   for (int j = 0; j < k; ++j) {
     LaunchTimer tm(ctx, MLCT_KERNEL_SLQ_SPMM);
-    HIPCHK(ctx, launch_slq_spmm(s, op->csr, W1, U, st->s_cur, plan, hub, P));
+    HIPCHK(ctx, launch_slq_spmm(s, op->csr, W1, U, st->s_cur, plan, P));
     tm.done();
     HIPCHK(ctx, launch_reduce_partials(s, P, 1, 2, plan.ngroups, kBlockProbes, D));
     HIPCHK(ctx, launch_slq_alpha(s, D, j, st));

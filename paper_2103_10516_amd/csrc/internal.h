@@ -234,6 +234,16 @@ CsrStepPlan plan_csr(int64_t d, int max_groups = 0);
 template <typename T>
 hipError_t launch_probe_init(hipStream_t s, T* v0, int64_t d, ProbeSrc src,
                              const CsrStepPlan& plan, double* part0);
+// Rows longer than kHubLen: sorted row ids, the first chunk of each and each
+// chunk's entries [cs, ce).
+struct HubRows {
+  const int32_t* rows;
+  const int32_t* c0;
+  const int32_t* cs;
+  const int32_t* ce;
+  int n;
+};
+
 // One probe block of a batch (FP32, 64 probes) over one CSR operator.
 struct BatchBlock {
   const int32_t* rowptr;
@@ -247,6 +257,7 @@ struct BatchBlock {
   double alpha, beta;
   int steps, ngroups, rows_per_group;
   const int32_t* band;  // the operator's row bands for ngroups, or nullptr
+  HubRows hubs;
   int64_t group_base;  // first workgroup of this block in the launch grid
 };
 hipError_t launch_probe_init_batched(hipStream_t s, const BatchBlock* tab, int nblocks,
@@ -264,7 +275,7 @@ struct XcdLaunch {
   int64_t slots[8];
 };
 // zmode 0 or 1 (regenerated probes); step >= 1; maxnz: the longest row of
-// the blocks' operators (above 8: the generic loop for long rows); grid =
+// the blocks' operators (above 8: the form for rows of any length); grid =
 // 8 x max slots[x]
 hipError_t launch_csr_step_batched(hipStream_t s, const BatchBlock* tab, const int32_t* xblk,
                                    const int32_t* xg0, const int64_t* xbase,
@@ -288,12 +299,10 @@ hipError_t launch_csr_batch_persistent(hipStream_t s, const BatchBlock* tab,
 int csr_batch_persistent_per_xcd(bool pattern, int maxnz, int zmode);
 // zmode: 0 = dots with V_k (symmetric form), 1 = regenerated Rademacher z,
 // 2 = explicit z entries.  has_prev = false for the first step (no V_prev).
-// hub_part: workspace of op->hub_chunks x 64 elements of T (unused without
-// hub rows); the step first launches the hub chunk reduction into it.
 template <typename T>
 hipError_t launch_csr_step(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
                            bool has_prev, int zmode, ProbeSrc src, const CsrStepPlan& plan,
-                           void* hub_part, double* part);
+                           double* part);
 // Gram operator A = X^T X + lambda I, one step: W = X V_k (rows x 64), then
 // V_new = ca X^T W + cb V_k [- V_prev] with the moments (cb includes
 // ca * lambda).  plan_rows / plan_cols: bands over X's rows / columns.
@@ -301,7 +310,7 @@ template <typename T>
 hipError_t launch_gram_csr_step(hipStream_t s, const CsrMat& X, const CsrMat& XT, const T* vk,
                                 T* vm, T* W, T ca, T cb, bool has_prev, int zmode, ProbeSrc src,
                                 const CsrStepPlan& plan_rows, const CsrStepPlan& plan_cols,
-                                void* hubx_part, void* hubt_part, double* part);
+                                double* part);
 // Rows longer than kHubLen as (row, start, end) triples, unordered; count is
 // incremented once per such row (entries past cap are not written).
 // Equal-work row bands: band[g] = the first row r with
@@ -376,8 +385,7 @@ struct SlqState {
   int kend[64];                           // diagonal entries kept per probe
 };
 hipError_t launch_slq_spmm(hipStream_t s, const CsrMat& m, const double* w, double* u,
-                           const double* sdev, const CsrStepPlan& plan, void* hub_part,
-                           double* part);
+                           const double* sdev, const CsrStepPlan& plan, double* part);
 hipError_t launch_slq_update(hipStream_t s, double* U, const double* W1, const double* W0,
                              const SlqState* st, int j, int64_t d, const CsrStepPlan& plan,
                              double* part);

@@ -48,11 +48,11 @@ constexpr int kTailHubs = 2;  // the generic loop, and hub partials past kHubLen
 
 template <typename P>
 __device__ __forceinline__ void store_partials(P a1, P a2, int g, int ngroups,
-                                               P* __restrict__ part) {
+                                               P* __restrict__ part, int probe = lane_id()) {
   __shared__ P sh[2][kWaves][64];
   const int lane = lane_id(), wave = wave_id();
-  sh[0][wave][lane] = a1;
-  sh[1][wave][lane] = a2;
+  sh[0][wave][probe] = a1;
+  sh[1][wave][probe] = a2;
   __syncthreads();
   if (wave == 0) {
     P s1 = sh[0][0][lane], s2 = sh[1][0][lane];
@@ -226,42 +226,6 @@ struct TriEpi {
       if (__builtin_expect(own == kY16Sentinel, 0)) own = hs.side[(int64_t)hs.slot(i) * 64 + lane];
       a1 += (long long)own * acc;
     }
-  }
-};
-
-// First product of a Gram step: the row sums are stored (W = X V_k), no
-// recurrence, no partials.
-template <typename T>
-struct StoreEpi {
-  using Part = double;
-  static constexpr bool kOwn = false;
-  static constexpr bool kParts = false;
-  T* out;
-  double a1 = 0.0, a2 = 0.0;
-  __device__ explicit StoreEpi(T* o) : out(o) {}
-  __device__ __forceinline__ T prev(int64_t) const { return T(0); }
-  __device__ __forceinline__ double part1() const { return a1; }
-  __device__ __forceinline__ double part2() const { return a2; }
-  __device__ __forceinline__ void finish(int64_t i, T acc, T, T, int) { out[i * 64 + lane_id()] = acc; }
-};
-
-// SpMM of a Lanczos step (FP64, lane = probe): u = s (A w_j) stored, with
-// s = 1 / |w_j| per probe, and partials of (s w_j) . u (the Jacobi diagonal).
-struct SlqEpi {
-  using Part = double;
-  static constexpr bool kOwn = true;
-  static constexpr bool kParts = true;
-  double* out;
-  double s;
-  double a1 = 0.0, a2 = 0.0;
-  __device__ SlqEpi(double* o, const double* sdev) : out(o), s(sdev[lane_id()]) {}
-  __device__ __forceinline__ double prev(int64_t) const { return 0.0; }
-  __device__ __forceinline__ double part1() const { return a1; }
-  __device__ __forceinline__ double part2() const { return a2; }
-  __device__ __forceinline__ void finish(int64_t i, double acc, double xi, double, int) {
-    const double u = s * acc;
-    out[i * 64 + lane_id()] = u;
-    a1 += (s * xi) * u;
   }
 };
 
@@ -766,16 +730,16 @@ __device__ __forceinline__ void csr_step_wg(
     store_partials<typename Epi::Part>(epi.part1(), epi.part2(), g, ngroups, part);
 }
 
-template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, bool OFF32, int TAIL>
+template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, bool OFF32>
 __global__ __launch_bounds__(kThreads) void csr_step_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
     const float* __restrict__ val, int64_t d, int64_t nnz, const T* __restrict__ vk,
-    T* __restrict__ vm, T ca, T cb, ProbeSrc src, HubView hub, CsrStepPlan plan,
-    double* __restrict__ part) {
-  RecEpi<T, ZMODE, HAS_PREV, false, TAIL == kTailNone ? 4 : 1> epi(ca, cb, vm, src);
-  csr_step_wg<T, PATTERN, MAXNZ, OFF32, TAIL, false>(rowptr, col, val, d, d, nnz,
-                                                     RowReader<T, OFF32>(vk, d, lane_id()),
-                                                     nullptr, epi, hub, plan, part, blockIdx.x);
+    T* __restrict__ vm, T ca, T cb, ProbeSrc src, CsrStepPlan plan, double* __restrict__ part) {
+  RecEpi<T, ZMODE, HAS_PREV, false, 4> epi(ca, cb, vm, src);
+  const HubView nohub{nullptr, nullptr, 0, nullptr};
+  csr_step_wg<T, PATTERN, MAXNZ, OFF32, kTailNone, false>(
+      rowptr, col, val, d, d, nnz, RowReader<T, OFF32>(vk, d, lane_id()), nullptr, epi, nohub, plan,
+      part, blockIdx.x);
 }
 
 // ---- wide form of the step ------------------------------------------------------
@@ -795,8 +759,9 @@ __global__ __launch_bounds__(kThreads) void csr_step_kernel(
 // class (row index in the group mod PPL, one class per lane group) and the
 // classes added in order; in FP32 that is the order of RecEpi with CLS = 4,
 // so this kernel and the lane = probe body give the same bits.  With SLQ
-// the rows are the product of a Lanczos step instead (the SlqEpi epilogue:
-// u = s (A w) stored, partials of (s w) . u; FP64, no recurrence).
+// the rows are the product of a Lanczos step instead (u = s (A w) stored,
+// s = 1 / |w| per probe, partials of (s w) . u, the Jacobi diagonal; FP64, no
+// recurrence).
 template <typename T>
 struct WideVec;
 template <>
@@ -819,6 +784,11 @@ struct WideRows {
       rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(b), (short)0,
                                                (int)(uint32_t)(d * 64 * sizeof(T)), 0x00020000);
     lane_off = (uint32_t)sub * 16;
+  }
+  // the lane's probes of the block row at byte offset off (past the block: 0)
+  __device__ __forceinline__ V at(uint32_t off) const {
+    return __builtin_bit_cast(
+        V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + lane_off, 0, 0));
   }
   // the lane's probes of block row j
   __device__ __forceinline__ V operator()(int64_t j) const {
@@ -1088,50 +1058,411 @@ csr_step_wide_kernel(
                                                         xcd_band(blockIdx.x, plan.ngroups), sh);
 }
 
+// ---- rows of any length ---------------------------------------------------------
+// The same step for operators with rows past the straight-line capacity
+// (power-law graphs, the two products of a sparse Gram step, Lanczos
+// products on such rows).  A lane holds 16 bytes of probes (PPL of them) and
+// a group of LPR = 64 / PPL lanes, a slot, walks one row, so a wave sums PPL
+// rows at once: a gathered row of V costs 1 / PPL of a load, one lane
+// broadcast and one add for its address and PPL fma, about 2 instructions
+// against the 10 of one row at a time with lane = probe, which was bound by
+// issuing them.  The lanes of a slot load 16 column indices at a time (the
+// next 16 while the gathers of the current ones are in flight); entry t is
+// spread over the slot by a DPP broadcast within 16 lanes, and a slot past
+// its row's end gathers out of range, which costs no memory access.  Each
+// row's sum has one fma per entry in entry order, and the moments are summed
+// per probe over a wave's rows in order, as with lane = probe.
+//
+// Rows longer than kHubLen are summed by the whole workgroup of their band:
+// chunks of kHubChunk entries, one per slot, each row's chunk sums added in
+// order (one row after the other left most slots idle: 1.3 times the step's
+// time on a graph of 10^6 vertices).
+//
+// Bound by the gathers themselves: from one XCD's L2 they run at about 100 G
+// rows of 256 bytes per second, from beyond it at 30 G (7.6 TB/s), measured
+// with a bare gather loop.  Measured on Chung-Lu graphs (64 probes, FP32, us
+// per step, one row at a time with a launch for the long rows' chunks before
+// -> now): d = 16,000 71 -> 33, 62,500 77 -> 40, 250,000 179 -> 154, 10^6
+// 741 -> 694 (5.9 TB/s of gathered rows); the batch of 64 graphs of 2,048 to
+// 65,536 vertices 176 -> 75 ms.
+enum { kOpRec = 0, kOpStore = 1, kOpSlq = 2 };
+
+// First hub row at or past row r, by a 64-way search over the wave's lanes
+// (two loads deep up to 4,096 rows; a binary search's chain of loads takes
+// longer than a short band).
+__device__ __forceinline__ int hub_lower(const HubRows& h, int64_t r) {
+  int lo = 0, hi = h.n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) / 64;
+    const int i = lo + lane_id() * step;
+    const int cnt = __popcll(__ballot(i < hi && h.rows[min(i, h.n - 1)] < r));
+    if (cnt == 0) break;
+    hi = min(hi, lo + cnt * step);
+    lo += (cnt - 1) * step + 1;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
+
+// Lane I of each row of 16 lanes, in all of them.
+template <int I>
+__device__ __forceinline__ int bcast16(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xf, 0xf, false);
+}
+
+// The slots' PPL x PPL exchange: element e of slot q goes to slot e, element q
+// (a lane had PPL probes of its slot's row, and has one probe of PPL rows).
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void slot_transpose(WideVec<float>::V& v) {
+  uint32_t x[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(v[e]);
+  swap32(x[0], x[2]);
+  swap32(x[1], x[3]);
+  swap16(x[0], x[1]);
+  swap16(x[2], x[3]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(x[e]);
+}
+__device__ __forceinline__ void slot_transpose(WideVec<double>::V& v) {
+  uint2 a = __builtin_bit_cast(uint2, (double)v[0]), b = __builtin_bit_cast(uint2, (double)v[1]);
+  swap32(a.x, b.x);
+  swap32(a.y, b.y);
+  v[0] = __builtin_bit_cast(double, a);
+  v[1] = __builtin_bit_cast(double, b);
+}
+
+// rsh: log2 of the rows of a group (a wave's consecutive rows).
+// OP kOpRec: the recurrence over rows 0 .. d - 1 (gathers from vk, own rows
+// from vown), kOpStore: the product alone into vm (normal stores: it is
+// gathered next), kOpSlq: the product of a Lanczos step.
+template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, bool OFF32, int OP = kOpRec>
+__device__ __forceinline__ void long_band(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+    const float* __restrict__ val, int64_t d, int64_t dv, const T* __restrict__ vk,
+    const T* __restrict__ vown, T* __restrict__ vm, T ca, T cb, const ProbeSrc& src,
+    const HubRows& hubs, int rsh, const CsrStepPlan& plan, double* __restrict__ part, int g,
+    const double* sdev = nullptr) {
+  using V = typename WideVec<T>::V;
+  constexpr int PPL = 16 / (int)sizeof(T);
+  constexpr int LPR = 64 / PPL;
+  constexpr int kSlots = kWaves * PPL;
+  constexpr uint32_t kRowBytes = 64 * sizeof(T);
+  // past every block whose size OFF32 admits, and off + 16 sub cannot wrap
+  constexpr uint32_t kOut = 0u - kRowBytes;
+  const int lane = lane_id(), wave = wave_id();
+  const int q = lane / LPR, sub = lane % LPR, l16 = lane & 15;
+  const int64_t r0 = plan.band ? (int64_t)plan.band[g] : (int64_t)g * plan.rows_per_group;
+  const int64_t r1 = plan.band ? (int64_t)plan.band[g + 1]
+                               : min<int64_t>(r0 + plan.rows_per_group, d);
+  const WideRows<T, OFF32> rd(vk, dv, sub);
+  T* vm_l = vm + sub * PPL;
+  const T* own_l = vown + sub * PPL;
+  // moment partials of probe `probe` (rows in order)
+  const int probe = PPL * sub + q;
+  double m1 = 0.0, m2 = 0.0;
+  double sc[PPL];
+  if constexpr (OP == kOpSlq) {
+#pragma unroll
+    for (int e = 0; e < PPL; ++e) sc[e] = sdev[PPL * sub + e];
+  }
+  uint64_t word = 0, key = 0;
+  int64_t cached = -1;
+  if constexpr (ZMODE == 1) key = sm_output(src.seed, (uint64_t)(src.first_id + probe));
+
+  // the slot's next 16 entries from `base` of its row (start s, n entries):
+  // row offsets (OFF32) or columns, and weights; past the end: out of range,
+  // weight 0
+  auto load16 = [&](int s, int n, int base, int& o, float& w) {
+    const bool in = base + l16 < n;
+    int j = 0;
+    w = 0.f;
+    if (in) {
+      j = col[(int64_t)s + base + l16];
+      if (!PATTERN) w = val[(int64_t)s + base + l16];
+    }
+    o = OFF32 ? (in ? (int)((uint32_t)j * kRowBytes) : (int)kOut) : j;
+  };
+  // N of those entries into acc; `after` issues what the wave needs next
+  // behind the gathers
+  auto sum_n = [&](auto nc, V& acc, int o, float w, int left, auto&& after) {
+    constexpr int N = decltype(nc)::value;
+    V x[N];
+    static_for<N>([&](auto t) {
+      constexpr int I = decltype(t)::value;
+      if constexpr (OFF32)
+        x[I] = rd.at((uint32_t)bcast16<I>(o));
+      else
+        x[I] = rd(bcast16<I>(o));
+    });
+    after();
+    // every gather is in flight before the first is used
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<N>([&](auto t) {
+      constexpr int I = decltype(t)::value;
+      if constexpr (!OFF32) x[I] = I < left ? x[I] : V{};
+      const T wt = PATTERN ? T(1) : (T)__int_as_float(bcast16<I>(__float_as_int(w)));
+#pragma unroll
+      for (int e = 0; e < PPL; ++e) acc[e] = PATTERN ? acc[e] + x[I][e] : fma(wt, x[I][e], acc[e]);
+    });
+  };
+  using I4 = std::integral_constant<int, 4>;
+  using I8 = std::integral_constant<int, 8>;
+  using I16 = std::integral_constant<int, 16>;
+  // the slots' sums over their n entries from s (n <= kHubChunk, uniform in a
+  // slot), the first 16 already loaded; `last` as `after` of the last part
+  auto sum_row = [&](V& acc, int s, int n, int o, float w, auto&& last) {
+    int mx = 0;
+#pragma unroll
+    for (int k = 0; k < PPL; ++k) mx = max(mx, read_lane(n, k * LPR));
+    int base = 0;
+    while (mx - base > 16) {
+      int on = 0;
+      float wn = 0.f;
+      sum_n(I16(), acc, o, w, n - base, [&] { load16(s, n, base + 16, on, wn); });
+      o = on;
+      w = wn;
+      base += 16;
+    }
+    if (mx - base > 8) sum_n(I16(), acc, o, w, n - base, last);
+    else if (mx - base > 4) sum_n(I8(), acc, o, w, n - base, last);
+    else sum_n(I4(), acc, o, w, n - base, last);
+  };
+  // the slot's new row from its sum
+  auto update = [&](int64_t row, const V& acc, const V& xi, const V& xp) {
+    V vn;
+#pragma unroll
+    for (int e = 0; e < PPL; ++e) {
+      if constexpr (OP == kOpStore) {
+        vn[e] = acc[e];
+      } else if constexpr (OP == kOpSlq) {
+        vn[e] = sc[e] * acc[e];
+      } else {
+        T v = fma(ca, acc[e], cb * xi[e]);
+        if (HAS_PREV) v -= xp[e];
+        vn[e] = v;
+      }
+    }
+    if constexpr (OP == kOpRec)
+      __builtin_nontemporal_store(vn, reinterpret_cast<V*>(vm_l + row * 64));
+    else
+      *reinterpret_cast<V*>(vm_l + row * 64) = vn;
+    return vn;
+  };
+  // moment partials of the wave's PPL rows from row0 on (zeros: no row): the
+  // slots exchange their rows so that a lane has one probe of all of them,
+  // and adds them in row order
+  auto moments = [&](int64_t row0, V xi, V vn) {
+    if constexpr (OP == kOpSlq) {
+#pragma unroll
+      for (int e = 0; e < PPL; ++e) xi[e] = sc[e] * xi[e];
+    }
+    slot_transpose(vn);
+    if constexpr (ZMODE == 0) slot_transpose(xi);
+#pragma unroll
+    for (int r = 0; r < PPL; ++r) {
+      if constexpr (ZMODE == 0) {
+        m1 += (double)xi[r] * (double)vn[r];
+        if constexpr (OP == kOpRec) m2 += (double)vn[r] * (double)vn[r];
+      } else if constexpr (ZMODE == 1) {
+        const int64_t c = (row0 + r) >> 6;
+        if (c != cached) {
+          word = sm_output(key, (uint64_t)c);
+          cached = c;
+        }
+        m1 += sign_from_word<double>(word, row0 + r) * (double)vn[r];
+      } else {
+        const bool in = probe < src.active && row0 + r < r1;
+        const double z = in ? (double)src.entries[(row0 + r) * src.ld + src.first_id + probe] : 0.0;
+        m1 += z * (double)vn[r];
+      }
+    }
+  };
+  // V_k and V_prev of the slot's row (a hub row: its new row, already there)
+  auto load_own = [&](int64_t row, bool hub, V& xi, V& xp) {
+    if constexpr (OP != kOpStore) {
+      xi = *reinterpret_cast<const V*>(own_l + row * 64);
+      if (HAS_PREV || hub)
+        xp = __builtin_nontemporal_load(reinterpret_cast<const V*>(vm_l + row * 64));
+    }
+  };
+
+  if (hubs.n > 0 && r1 > r0) {
+    __shared__ V shub[kSlots][LPR], scarry[LPR];
+    const int slot = wave * PPL + q;
+    int hr = hub_lower(hubs, r0);  // the first row not yet ended
+    const int h1 = hub_lower(hubs, r1);
+    if (h1 > hr) {
+      const int ce = hubs.c0[h1];
+      for (int c0 = hubs.c0[hr]; c0 < ce; c0 += kSlots) {
+        // one chunk per slot
+        const int c = c0 + slot;
+        const int cs = c < ce ? hubs.cs[c] : 0;
+        const int n = c < ce ? hubs.ce[c] - cs : 0;
+        int o;
+        float w;
+        V acc = V{};
+        load16(cs, n, 0, o, w);
+        sum_row(acc, cs, n, o, w, [] {});
+        shub[slot][sub] = acc;
+        __syncthreads();
+        // one row per slot: its chunks of this round behind what earlier
+        // rounds left; the last row may go on in the next round
+        const int h = hr + slot;
+        const int b = h < h1 ? hubs.c0[h] : INT_MAX;
+        bool ended = false;
+        V tot = V{};
+        if (b < c0 + kSlots) {
+          const int e = hubs.c0[h + 1];
+          ended = e <= c0 + kSlots;
+          if (b < c0) tot = scarry[sub];
+          const int j1 = min(e, c0 + kSlots) - c0;
+          for (int j = max(b - c0, 0); j < j1; ++j) tot += shub[j][sub];
+          if (ended) {
+            const int64_t row = hubs.rows[h];
+            V xi = V{}, xp = V{};
+            load_own(row, false, xi, xp);
+            update(row, tot, xi, xp);
+          }
+        }
+        const int done = __syncthreads_count(ended && sub == 0);
+        if (b < c0 + kSlots && !ended) scarry[sub] = tot;
+        hr += done;
+        // (the next round's first barrier orders the carry before its use)
+      }
+    }
+  }
+
+  // wave w takes the groups w, w + kWaves, ... of 1 << rsh rows, PPL at a time
+  const int parts = (1 << rsh) / PPL;
+  const int64_t ngrp = r1 > r0 ? (r1 - r0 + (1 << rsh) - 1) >> rsh : 0;
+  const int64_t nk = ngrp > wave ? (ngrp - wave + kWaves - 1) / kWaves * parts : 0;
+  auto first_row = [&](int64_t k) {
+    return r0 + (((k / parts) * kWaves + wave) << rsh) + (k % parts) * PPL;
+  };
+  if (nk > 0) {
+    // row, start and length of the slot's k-th row (length 0: none, or a row
+    // that the hub pass took)
+    auto extent = [&](int64_t k, int64_t& row, bool& live, bool& hub, int& s, int& n) {
+      row = first_row(k) + q;
+      live = row < r1;
+      row = live ? row : r1 - 1;
+      s = rowptr[row];
+      n = live ? rowptr[row + 1] - s : 0;
+      hub = n > kHubLen;
+      if (hub) n = 0;
+    };
+    int64_t row, row_n = 0;
+    bool live, hub, live_n = false, hub_n = false;
+    int s, n, s_n = 0, n_n = 0;
+    extent(0, row, live, hub, s, n);
+    if (nk > 1) extent(1, row_n, live_n, hub_n, s_n, n_n);
+    int o, o_n = 0;
+    float w, w_n = 0.f;
+    load16(s, n, 0, o, w);
+    for (int64_t k = 0; k < nk; ++k) {
+      V acc = V{}, xi = V{}, xp = V{};
+      int64_t row_f = row;
+      bool live_f = false, hub_f = false;
+      int s_f = 0, n_f = 0;
+      sum_row(acc, s, n, o, w, [&] {
+        load_own(row, hub, xi, xp);
+        load16(s_n, n_n, 0, o_n, w_n);
+        if (k + 2 < nk) extent(k + 2, row_f, live_f, hub_f, s_f, n_f);
+      });
+      V vn = xp;
+      if (live && !hub) vn = update(row, acc, xi, xp);
+      if constexpr (OP != kOpStore) {
+        if (!live) vn = xi = V{};
+        moments(first_row(k), xi, vn);
+      }
+      row = row_n;
+      live = live_n;
+      hub = hub_n;
+      s = s_n;
+      n = n_n;
+      o = o_n;
+      w = w_n;
+      row_n = row_f;
+      live_n = live_f;
+      hub_n = hub_f;
+      s_n = s_f;
+      n_n = n_f;
+    }
+  }
+  if constexpr (OP != kOpStore)
+    store_partials<double>(m1, m2, g, plan.ngroups, part, probe);
+}
+
+// (at least 4 waves per SIMD, two workgroups per CU)
+template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, bool OFF32>
+__global__ __launch_bounds__(kThreads, 4) void csr_step_long_kernel(
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+    const float* __restrict__ val, int64_t d, const T* __restrict__ vk, T* __restrict__ vm, T ca,
+    T cb, ProbeSrc src, HubRows hubs, CsrStepPlan plan, double* __restrict__ part) {
+  long_band<T, PATTERN, ZMODE, HAS_PREV, OFF32>(rowptr, col, val, d, d, vk, vk, vm, ca, cb, src,
+                                                hubs, 2, plan, part,
+                                                xcd_band(blockIdx.x, plan.ngroups));
+}
+
 // Gram step, first product: W = X V_k over X's rows (V_k has dv = X's
 // column count rows).
-template <typename T, bool PATTERN, int MAXNZ, bool OFF32, int TAIL>
-__global__ __launch_bounds__(kThreads) void gram_pass1_kernel(
+template <typename T, bool PATTERN, bool OFF32>
+__global__ __launch_bounds__(kThreads, 4) void gram_pass1_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const float* __restrict__ val, int64_t d, int64_t dv, int64_t nnz, const T* __restrict__ vk,
-    T* __restrict__ W, HubView hub, CsrStepPlan plan) {
-  StoreEpi<T> epi(W);
-  csr_step_wg<T, PATTERN, MAXNZ, OFF32, TAIL, false>(rowptr, col, val, d, dv, nnz,
-                                                     RowReader<T, OFF32>(vk, dv, lane_id()),
-                                                     nullptr, epi, hub, plan, nullptr, blockIdx.x);
+    const float* __restrict__ val, int64_t d, int64_t dv, const T* __restrict__ vk,
+    T* __restrict__ W, HubRows hubs, CsrStepPlan plan) {
+  long_band<T, PATTERN, 0, false, OFF32, kOpStore>(rowptr, col, val, d, dv, vk, vk, W, T(0), T(0),
+                                                   ProbeSrc{}, hubs, 2, plan, nullptr,
+                                                   xcd_band(blockIdx.x, plan.ngroups));
 }
 
 // Gram step, second product with the recurrence: V_new = ca X^T W + cb V_k
 // [- V_prev] over X^T's rows, gathering from W, own rows from V_k.
-template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, bool OFF32, int TAIL>
-__global__ __launch_bounds__(kThreads) void gram_pass2_kernel(
+template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, bool OFF32>
+__global__ __launch_bounds__(kThreads, 4) void gram_pass2_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const float* __restrict__ val, int64_t d, int64_t dv, int64_t nnz, const T* __restrict__ W,
-    const T* __restrict__ vk, T* __restrict__ vm, T ca, T cb, ProbeSrc src, HubView hub,
-    CsrStepPlan plan, double* __restrict__ part) {
-  RecEpi<T, ZMODE, HAS_PREV> epi(ca, cb, vm, src);
-  csr_step_wg<T, PATTERN, MAXNZ, OFF32, TAIL, true>(rowptr, col, val, d, dv, nnz,
-                                                    RowReader<T, OFF32>(W, dv, lane_id()), vk,
-                                                    epi, hub, plan, part, blockIdx.x);
+    const float* __restrict__ val, int64_t d, int64_t dv, const T* __restrict__ W,
+    const T* __restrict__ vk, T* __restrict__ vm, T ca, T cb, ProbeSrc src, HubRows hubs,
+    int rsh, CsrStepPlan plan, double* __restrict__ part) {
+  long_band<T, PATTERN, ZMODE, HAS_PREV, OFF32>(rowptr, col, val, d, dv, W, vk, vm, ca, cb, src,
+                                                hubs, rsh, plan, part,
+                                                xcd_band(blockIdx.x, plan.ngroups));
 }
 
-template <bool PATTERN, int MAXNZ, int TAIL>
+// Lanczos product u = s (A w): rows within the straight-line capacity take
+// the wide form, others (MAXNZ 0) the form for rows of any length.
+template <bool PATTERN, int MAXNZ, bool OFF32>
 __global__ __launch_bounds__(kThreads) void slq_spmm_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
     const float* __restrict__ val, int64_t d, int64_t nnz, const double* __restrict__ w,
-    double* __restrict__ u, const double* __restrict__ sdev, HubView hub, CsrStepPlan plan,
+    double* __restrict__ u, const double* __restrict__ sdev, HubRows hubs, CsrStepPlan plan,
     double* __restrict__ part) {
-  if constexpr (TAIL == kTailNone) {
-    // rows within the straight-line capacity: the wide form, 2 probes per lane
+  const int g = xcd_band(blockIdx.x, plan.ngroups);
+  if constexpr (MAXNZ > 0) {
     __shared__ WidePartials<double> sh;
-    wide_band<double, PATTERN, 0, false, MAXNZ, false, true>(
-        rowptr, col, val, d, nnz, w, u, 0.0, 0.0, ProbeSrc{}, plan, part,
-        xcd_band(blockIdx.x, plan.ngroups), sh, sdev);
+    wide_band<double, PATTERN, 0, false, MAXNZ, false, true>(rowptr, col, val, d, nnz, w, u, 0.0,
+                                                             0.0, ProbeSrc{}, plan, part, g, sh,
+                                                             sdev);
   } else {
-    SlqEpi epi(u, sdev);
-    csr_step_wg<double, PATTERN, MAXNZ, false, TAIL, false>(
-        rowptr, col, val, d, d, nnz, RowReader<double, false>(w, d, lane_id()), nullptr, epi,
-        hub, plan, part, blockIdx.x);
+    long_band<double, PATTERN, 0, false, OFF32, kOpSlq>(rowptr, col, val, d, d, w, w, u, 0.0, 0.0,
+                                                        ProbeSrc{}, hubs, 2, plan, part, g, sdev);
   }
 }
 
@@ -1172,22 +1503,6 @@ __global__ __launch_bounds__(256) void tri_hub_kernel(const int32_t* __restrict_
     v = row_dot_generic<int32_t, true>(col, nullptr, Y16Reader<OFF32>(yin, d, lane, hs), cs[c],
                                        ce[c]);
   out[(int64_t)c * 64 + lane] = v;
-}
-
-// Chunk partials of the hub rows: one wave per chunk of at most kHubChunk
-// entries, sum over the chunk of A[i][j] V_k[j] (exact for int32).
-template <typename T, bool PATTERN, bool OFF32>
-__global__ __launch_bounds__(256) void csr_hub_kernel(const int32_t* __restrict__ col,
-                                                      const float* __restrict__ val, int64_t d,
-                                                      const T* __restrict__ vk,
-                                                      const int32_t* __restrict__ cs,
-                                                      const int32_t* __restrict__ ce,
-                                                      int nchunks, T* __restrict__ out) {
-  const int c = blockIdx.x * 4 + wave_id();
-  if (c >= nchunks) return;
-  const int lane = lane_id();
-  const RowReader<T, OFF32> rd(vk, d, lane);
-  out[(int64_t)c * 64 + lane] = row_dot_generic<T, PATTERN>(col, val, rd, cs[c], ce[c]);
 }
 
 // Equal-work row bands by binary search on rowptr[r] + kBandRowCost * r.
@@ -1241,8 +1556,8 @@ __device__ __forceinline__ int find_block(const BatchBlock* __restrict__ tab, in
   return lo;
 }
 
-template <bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, int TAIL>
-__global__ __launch_bounds__(kThreads) void csr_step_batched_kernel(
+template <bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ>
+__global__ __launch_bounds__(kThreads, MAXNZ == 0 ? 4 : 1) void csr_step_batched_kernel(
     const BatchBlock* __restrict__ tab, const int32_t* __restrict__ xblk,
     const int32_t* __restrict__ xg0, const int64_t* __restrict__ xbase, XcdLaunch xl, int s) {
   const int x = blockIdx.x & 7;
@@ -1255,27 +1570,22 @@ __global__ __launch_bounds__(kThreads) void csr_step_batched_kernel(
   }
   const int bi = __builtin_amdgcn_readfirstlane(xblk[lo]);
   const BatchBlock& B = tab[bi];
-  // band g of the block; bid is the index whose xcd_band is g
-  const int g = xg0[lo] + (int)(slot - xbase[lo]);
-  const int per = B.ngroups >> 3;
-  const int bid = (g % per) * 8 + g / per;
+  const int g = xg0[lo] + (int)(slot - xbase[lo]);  // band of the block
   const float* vk = (s - 1) & 1 ? B.v1 : B.v0;
   float* vm = s & 1 ? B.v1 : B.v0;
   const float ca = (float)(HAS_PREV ? 2.0 * B.alpha : B.alpha);
   const float cb = (float)(HAS_PREV ? 2.0 * B.beta : B.beta);
   const CsrStepPlan plan{B.ngroups, B.rows_per_group, B.band};
   double* part = B.part + (size_t)s * 2 * B.ngroups * 64;
-  if constexpr (ZMODE <= 1 && TAIL == kTailNone) {
-    // the single-operator step's wide form (same bits)
+  // the single-operator step's forms (same bits)
+  if constexpr (MAXNZ > 0) {
     __shared__ WidePartials<float> sh;
     wide_band<float, PATTERN, ZMODE, HAS_PREV, MAXNZ, true>(B.rowptr, B.col, B.val, B.d, B.nnz, vk,
                                                              vm, ca, cb, B.src, plan, part, g, sh);
   } else {
-    RecEpi<float, ZMODE, HAS_PREV, false, TAIL == kTailNone ? 4 : 1> epi(ca, cb, vm, B.src);
-    const HubView nohub{nullptr, nullptr, 0, nullptr};
-    csr_step_wg<float, PATTERN, MAXNZ, true, TAIL, false>(
-        B.rowptr, B.col, B.val, B.d, B.d, B.nnz, RowReader<float, true>(vk, B.d, lane_id()),
-        nullptr, epi, nohub, plan, part, bid);
+    long_band<float, PATTERN, ZMODE, HAS_PREV, true>(B.rowptr, B.col, B.val, B.d, B.d, vk, vk, vm,
+                                                     ca, cb, B.src,
+                                                     B.hubs, 2, plan, part, g);
   }
 }
 
@@ -1327,8 +1637,8 @@ __device__ __forceinline__ bool persist_wait(const PersistLaunch& pl, int blk, i
 // workgroup's consecutive slots of one block share one wait and one
 // release (its arrivals are added together before it waits on another
 // block or leaves the step).
-template <bool PATTERN, int ZMODE, int MAXNZ, int TAIL>
-__global__ __launch_bounds__(kThreads) void csr_batch_persistent_kernel(
+template <bool PATTERN, int ZMODE, int MAXNZ>
+__global__ __launch_bounds__(kThreads, MAXNZ == 0 ? 4 : 1) void csr_batch_persistent_kernel(
     const BatchBlock* __restrict__ tab, const int32_t* __restrict__ xblk,
     const int32_t* __restrict__ xg0, const int64_t* __restrict__ xbase, PersistLaunch pl) {
   const int x = blockIdx.x & 7;
@@ -1350,8 +1660,6 @@ __global__ __launch_bounds__(kThreads) void csr_batch_persistent_kernel(
       const int bi = __builtin_amdgcn_readfirstlane(xblk[lo]);
       const BatchBlock& B = tab[bi];
       const int g = xg0[lo] + (int)(slot - xbase[lo]);
-      const int per = B.ngroups >> 3;
-      const int bid = (g % per) * 8 + g / per;
       if (bi != held) {
         if (pending) release(held, pending);
         pending = 0;
@@ -1363,16 +1671,14 @@ __global__ __launch_bounds__(kThreads) void csr_batch_persistent_kernel(
       const float ca = (float)(2.0 * B.alpha), cb = (float)(2.0 * B.beta);
       const CsrStepPlan plan{B.ngroups, B.rows_per_group, B.band};
       double* part = B.part + (size_t)s * 2 * B.ngroups * 64;
-      if constexpr (ZMODE <= 1 && TAIL == kTailNone) {
+      if constexpr (MAXNZ > 0) {
         __shared__ WidePartials<float> sh;
         wide_band<float, PATTERN, ZMODE, true, MAXNZ, true>(B.rowptr, B.col, B.val, B.d, B.nnz, vk,
                                                              vm, ca, cb, B.src, plan, part, g, sh);
       } else {
-        RecEpi<float, ZMODE, true, false, TAIL == kTailNone ? 4 : 1> epi(ca, cb, vm, B.src);
-        const HubView nohub{nullptr, nullptr, 0, nullptr};
-        csr_step_wg<float, PATTERN, MAXNZ, true, TAIL, false>(
-            B.rowptr, B.col, B.val, B.d, B.d, B.nnz, RowReader<float, true>(vk, B.d, lane_id()),
-            nullptr, epi, nohub, plan, part, bid);
+        long_band<float, PATTERN, ZMODE, true, true>(B.rowptr, B.col, B.val, B.d, B.d, vk, vk, vm,
+                                                     ca, cb, B.src,
+                                                     B.hubs, 2, plan, part, g);
       }
       __syncthreads();  // the step body's shared partial buffer is reused
       ++pending;
@@ -1401,120 +1707,87 @@ CsrStepPlan banded(const CsrMat& m, CsrStepPlan p) {
   return p;
 }
 
-template <typename T, bool PATTERN, int ZMODE, int MAXNZ, bool OFF32, int TAIL>
-hipError_t launch_step_t(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
-                         bool has_prev, ProbeSrc src, const CsrStepPlan& plan, const HubView& hub,
-                         double* part) {
-  const dim3 grid(plan.ngroups), block(kThreads);
-  if constexpr (ZMODE <= 1 && TAIL == kTailNone) {
-    if (has_prev)
-      csr_step_wide_kernel<T, PATTERN, ZMODE, true, MAXNZ, OFF32><<<grid, block, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, banded(m, plan), part);
-    else
-      csr_step_wide_kernel<T, PATTERN, ZMODE, false, MAXNZ, OFF32><<<grid, block, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, banded(m, plan), part);
-  } else {
-    if (has_prev)
-      csr_step_kernel<T, PATTERN, ZMODE, true, MAXNZ, OFF32, TAIL><<<grid, block, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, hub, banded(m, plan), part);
-    else
-      csr_step_kernel<T, PATTERN, ZMODE, false, MAXNZ, OFF32, TAIL><<<grid, block, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, hub, banded(m, plan), part);
-  }
-  return hipGetLastError();
-}
-
-// Whether gathers from a block of dv rows can use 32-bit offsets (4-byte
-// elements, block under 4 GiB).
+// Whether gathers from a block of dv rows can use 32-bit offsets (block under
+// 4 GiB).
 template <typename T>
 bool block_off32(int64_t dv) {
-  return sizeof(T) == 4 && (uint64_t)dv * 64 * sizeof(T) <= 0xFFFFFFFFull;
+  return (uint64_t)dv * 64 * sizeof(T) <= 0xFFFFFFFFull;
 }
 
-HubView hub_view(const CsrMat& m, void* hub_part) {
-  return HubView{m.hub_rows, m.hub_c0, m.hub_n, hub_part};
-}
-
-// Hub chunk partials of the gathered block v (dv rows) for this step (a
-// no-op without hub rows).
-template <typename T, bool PATTERN>
-hipError_t launch_hubs(hipStream_t s, const CsrMat& m, const T* v, int64_t dv, void* hub_part) {
-  if (m.hub_n == 0) return hipSuccess;
-  const int grid = (m.hub_chunks + 3) / 4;
-  T* out = static_cast<T*>(hub_part);
-  if constexpr (sizeof(T) == 4) {
-    if (block_off32<T>(dv)) {
-      csr_hub_kernel<T, PATTERN, true><<<grid, 256, 0, s>>>(m.col, m.val, dv, v, m.hub_cs,
-                                                           m.hub_ce, m.hub_chunks, out);
-      return hipGetLastError();
-    }
-  }
-  csr_hub_kernel<T, PATTERN, false><<<grid, 256, 0, s>>>(m.col, m.val, dv, v, m.hub_cs, m.hub_ce,
-                                                        m.hub_chunks, out);
-  return hipGetLastError();
+HubRows hub_rows(const CsrMat& m) {
+  return HubRows{m.hub_rows, m.hub_c0, m.hub_cs, m.hub_ce, m.hub_n};
 }
 
 // Row capacity of the straight-line path: the smallest of {4, 5, 8} that
-// holds the longest row.  When one does, every group takes the straight-line
-// path and the generic loop is not compiled in (kTailNone: it would hold
-// registers the straight-line path can use); else MAXNZ = 8 and longer rows
-// take the generic loop (kTailGen), and rows past kHubLen the hub partials
-// (kTailHubs).  FP32 blocks under 4 GiB use 32-bit gather offsets; FP64 (a
-// verification precision) uses one general instantiation.
-// F(MAXNZ, OFF32, TAIL) launches one instantiation.
+// holds the longest row, or 0 (rows of any length).  The straight-line path
+// in FP64 (a verification precision) uses one general instantiation; else
+// blocks under 4 GiB use 32-bit gather offsets.  F(MAXNZ, OFF32) launches one
+// instantiation.
 template <typename T, class F>
 hipError_t dispatch_shape(const CsrMat& m, int64_t dv, F&& f) {
+  using I0 = std::integral_constant<int, 0>;
   using I4 = std::integral_constant<int, 4>;
   using I5 = std::integral_constant<int, 5>;
   using I8 = std::integral_constant<int, 8>;
-  using None = std::integral_constant<int, kTailNone>;
-  using Gen = std::integral_constant<int, kTailGen>;
-  using Hubs = std::integral_constant<int, kTailHubs>;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  if (m.nnz < 1 || m.max_row_nnz > 8)
+    return block_off32<T>(dv) ? f(I0(), Yes()) : f(I0(), No());
   if constexpr (sizeof(T) == 4) {
     if (block_off32<T>(dv)) {
-      if (m.hub_n > 0) return f(I8(), std::true_type(), Hubs());
-      if (m.nnz > 0 && m.max_row_nnz <= 4) return f(I4(), std::true_type(), None());
-      if (m.nnz > 0 && m.max_row_nnz <= 5) return f(I5(), std::true_type(), None());
-      if (m.nnz > 0 && m.max_row_nnz <= 8) return f(I8(), std::true_type(), None());
-      return f(I8(), std::true_type(), Gen());
+      if (m.max_row_nnz <= 4) return f(I4(), Yes());
+      if (m.max_row_nnz <= 5) return f(I5(), Yes());
+      return f(I8(), Yes());
     }
   }
-  if (m.hub_n > 0) return f(I8(), std::false_type(), Hubs());
-  if (m.nnz > 0 && m.max_row_nnz <= 4) return f(I4(), std::false_type(), None());
-  if (m.nnz > 0 && m.max_row_nnz <= 5) return f(I5(), std::false_type(), None());
-  if (m.nnz > 0 && m.max_row_nnz <= 8) return f(I8(), std::false_type(), None());
-  return f(I8(), std::false_type(), Gen());
+  if (m.max_row_nnz <= 4) return f(I4(), No());
+  if (m.max_row_nnz <= 5) return f(I5(), No());
+  return f(I8(), No());
+}
+
+template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, bool OFF32>
+hipError_t launch_step_t(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
+                         ProbeSrc src, const CsrStepPlan& plan, double* part) {
+  const dim3 grid(plan.ngroups), block(kThreads);
+  const CsrStepPlan p = banded(m, plan);
+  if constexpr (MAXNZ == 0)
+    csr_step_long_kernel<T, PATTERN, ZMODE, HAS_PREV, OFF32><<<grid, block, 0, s>>>(
+        m.rowptr, m.col, m.val, m.nrows, vk, vm, ca, cb, src, hub_rows(m), p, part);
+  else if constexpr (ZMODE <= 1)
+    csr_step_wide_kernel<T, PATTERN, ZMODE, HAS_PREV, MAXNZ, OFF32><<<grid, block, 0, s>>>(
+        m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, p, part);
+  else
+    csr_step_kernel<T, PATTERN, ZMODE, HAS_PREV, MAXNZ, OFF32><<<grid, block, 0, s>>>(
+        m.rowptr, m.col, m.val, m.nrows, m.nnz, vk, vm, ca, cb, src, p, part);
+  return hipGetLastError();
 }
 
 template <typename T, bool PATTERN, int ZMODE>
 hipError_t launch_step_nz(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
-                          bool has_prev, ProbeSrc src, const CsrStepPlan& plan, void* hub_part,
-                          double* part) {
-  const HubView hub = hub_view(m, hub_part);
-  if (m.hub_n > 0) {
-    const hipError_t e = launch_hubs<T, PATTERN>(s, m, vk, m.ncols, hub_part);
-    if (e != hipSuccess) return e;
-  }
-  return dispatch_shape<T>(m, m.ncols, [&](auto mz, auto off32, auto tail) {
-    return launch_step_t<T, PATTERN, ZMODE, decltype(mz)::value, decltype(off32)::value,
-                         decltype(tail)::value>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub,
-                                                part);
+                          bool has_prev, ProbeSrc src, const CsrStepPlan& plan, double* part) {
+  return dispatch_shape<T>(m, m.ncols, [&](auto mz, auto off32) {
+    constexpr int MZ = decltype(mz)::value;
+    constexpr bool O = decltype(off32)::value;
+    return has_prev
+               ? launch_step_t<T, PATTERN, ZMODE, true, MZ, O>(s, m, vk, vm, ca, cb, src, plan, part)
+               : launch_step_t<T, PATTERN, ZMODE, false, MZ, O>(s, m, vk, vm, ca, cb, src, plan,
+                                                                part);
   });
 }
 
 template <typename T>
 hipError_t launch_step_any(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
                            bool has_prev, int zmode, ProbeSrc src, const CsrStepPlan& plan,
-                           void* hub_part, double* part) {
+                           double* part) {
   const bool pat = m.val == nullptr;
   if (pat) {
-    if (zmode == 0) return launch_step_nz<T, true, 0>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
-    if (zmode == 1) return launch_step_nz<T, true, 1>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
-    return launch_step_nz<T, true, 2>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
+    if (zmode == 0) return launch_step_nz<T, true, 0>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
+    if (zmode == 1) return launch_step_nz<T, true, 1>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
+    return launch_step_nz<T, true, 2>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
   }
-  if (zmode == 0) return launch_step_nz<T, false, 0>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
-  if (zmode == 1) return launch_step_nz<T, false, 1>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
-  return launch_step_nz<T, false, 2>(s, m, vk, vm, ca, cb, has_prev, src, plan, hub_part, part);
+  if (zmode == 0) return launch_step_nz<T, false, 0>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
+  if (zmode == 1) return launch_step_nz<T, false, 1>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
+  return launch_step_nz<T, false, 2>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
 }
 
 template <int PASS, bool OFF32>
@@ -1539,35 +1812,27 @@ hipError_t launch_tri_pass(hipStream_t s, const CsrMat& m, const CsrStepPlan& pl
 template <typename T, bool PATTERN, int ZMODE>
 hipError_t launch_gram_z(hipStream_t s, const CsrMat& X, const CsrMat& XT, const T* vk, T* vm,
                          T* W, T ca, T cb, bool has_prev, ProbeSrc src,
-                         const CsrStepPlan& pr, const CsrStepPlan& pc, void* hubx_part,
-                         void* hubt_part, double* part) {
-  hipError_t e = launch_hubs<T, PATTERN>(s, X, vk, X.ncols, hubx_part);
-  if (e != hipSuccess) return e;
-  const HubView hx = hub_view(X, hubx_part), ht = hub_view(XT, hubt_part);
-  e = dispatch_shape<T>(X, X.ncols, [&](auto mz, auto off32, auto tail) {
-    gram_pass1_kernel<T, PATTERN, decltype(mz)::value, decltype(off32)::value,
-                      decltype(tail)::value><<<pr.ngroups, kThreads, 0, s>>>(
-        X.rowptr, X.col, X.val, X.nrows, X.ncols, X.nnz, vk, W, hx, banded(X, pr));
+                         const CsrStepPlan& pr, const CsrStepPlan& pc, double* part) {
+  auto pass1 = [&](auto off32) {
+    gram_pass1_kernel<T, PATTERN, decltype(off32)::value><<<pr.ngroups, kThreads, 0, s>>>(
+        X.rowptr, X.col, X.val, X.nrows, X.ncols, vk, W, hub_rows(X), banded(X, pr));
     return hipGetLastError();
-  });
-  if (e != hipSuccess) return e;
-  e = launch_hubs<T, PATTERN>(s, XT, W, XT.ncols, hubt_part);
-  if (e != hipSuccess) return e;
-  return dispatch_shape<T>(XT, XT.ncols, [&](auto mz, auto off32, auto tail) {
-    if (has_prev)
-      gram_pass2_kernel<T, PATTERN, ZMODE, true, decltype(mz)::value, decltype(off32)::value,
-                        decltype(tail)::value><<<pc.ngroups, kThreads, 0, s>>>(
-          XT.rowptr, XT.col, XT.val, XT.nrows, XT.ncols, XT.nnz, W, vk, vm, ca, cb, src, ht,
-          banded(XT, pc), part);
-    else
-      gram_pass2_kernel<T, PATTERN, ZMODE, false, decltype(mz)::value, decltype(off32)::value,
-                        decltype(tail)::value><<<pc.ngroups, kThreads, 0, s>>>(
-          XT.rowptr, XT.col, XT.val, XT.nrows, XT.ncols, XT.nnz, W, vk, vm, ca, cb, src, ht,
-          banded(XT, pc), part);
+  };
+  const int rsh = XT.nnz > 0 && XT.max_row_nnz <= 5 ? 3 : 2;  // as the CSR step's groups
+  auto pass2 = [&](auto prev, auto off32) {
+    gram_pass2_kernel<T, PATTERN, ZMODE, decltype(prev)::value, decltype(off32)::value>
+        <<<pc.ngroups, kThreads, 0, s>>>(XT.rowptr, XT.col, XT.val, XT.nrows, XT.ncols, W, vk, vm,
+                                         ca, cb, src, hub_rows(XT), rsh, banded(XT, pc),
+                                         part);
     return hipGetLastError();
-  });
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  const hipError_t e = block_off32<T>(X.ncols) ? pass1(Yes()) : pass1(No());
+  if (e != hipSuccess) return e;
+  if (block_off32<T>(XT.ncols)) return has_prev ? pass2(Yes(), Yes()) : pass2(No(), Yes());
+  return has_prev ? pass2(Yes(), No()) : pass2(No(), No());
 }
-
 
 // ---- two recurrence steps per launch ------------------------------------------
 // For operators whose rows have at most 5 entries and whose columns lie
@@ -1763,18 +2028,18 @@ hipError_t launch_probe_init(hipStream_t s, T* v0, int64_t d, ProbeSrc src,
 template <typename T>
 hipError_t launch_csr_step(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T ca, T cb,
                            bool has_prev, int zmode, ProbeSrc src, const CsrStepPlan& plan,
-                           void* hub_part, double* part) {
-  return launch_step_any<T>(s, m, vk, vm, ca, cb, has_prev, zmode, src, plan, hub_part, part);
+                           double* part) {
+  return launch_step_any<T>(s, m, vk, vm, ca, cb, has_prev, zmode, src, plan, part);
 }
 
 template <typename T>
 hipError_t launch_gram_csr_step(hipStream_t s, const CsrMat& X, const CsrMat& XT, const T* vk,
                                 T* vm, T* W, T ca, T cb, bool has_prev, int zmode, ProbeSrc src,
                                 const CsrStepPlan& plan_rows, const CsrStepPlan& plan_cols,
-                                void* hubx_part, void* hubt_part, double* part) {
+                                double* part) {
 #define MLCT_GZ(P, Z)                                                                       \
   return launch_gram_z<T, P, Z>(s, X, XT, vk, vm, W, ca, cb, has_prev, src, plan_rows,      \
-                                plan_cols, hubx_part, hubt_part, part)
+                                plan_cols, part)
   if (X.val == nullptr) {
     if (zmode == 0) MLCT_GZ(true, 0);
     if (zmode == 1) MLCT_GZ(true, 1);
@@ -1789,7 +2054,7 @@ hipError_t launch_gram_csr_step(hipStream_t s, const CsrMat& X, const CsrMat& XT
 hipError_t launch_tri_step(hipStream_t s, const CsrMat& m, int pass, const CsrStepPlan& plan,
                            const uint64_t* zbits, int16_t* y, int32_t* side, void* hub_part,
                            long long* part) {
-  const HubView hub = hub_view(m, hub_part);
+  const HubView hub{m.hub_rows, m.hub_c0, m.hub_n, hub_part};
   const HubSide hs{m.hub_rows, m.hub_n, side};
   const bool off32 = (uint64_t)m.ncols * 64 * sizeof(int16_t) <= 0xFFFFFFFFull;
   if (m.hub_n > 0) {
@@ -1811,23 +2076,16 @@ hipError_t launch_tri_step(hipStream_t s, const CsrMat& m, int pass, const CsrSt
 }
 
 hipError_t launch_slq_spmm(hipStream_t s, const CsrMat& m, const double* w, double* u,
-                           const double* sdev, const CsrStepPlan& plan, void* hub_part,
-                           double* part) {
-  const bool pat = m.val == nullptr;
-  if (m.hub_n > 0) {
-    const hipError_t e = pat ? launch_hubs<double, true>(s, m, w, m.ncols, hub_part)
-                             : launch_hubs<double, false>(s, m, w, m.ncols, hub_part);
-    if (e != hipSuccess) return e;
-  }
-  const HubView hub = hub_view(m, hub_part);
-  return dispatch_shape<double>(m, m.ncols, [&](auto mz, auto, auto tail) {
-    constexpr int MZ = decltype(mz)::value, TL = decltype(tail)::value;
-    if (pat)
-      slq_spmm_kernel<true, MZ, TL><<<plan.ngroups, kThreads, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, w, u, sdev, hub, banded(m, plan), part);
+                           const double* sdev, const CsrStepPlan& plan, double* part) {
+  return dispatch_shape<double>(m, m.ncols, [&](auto mz, auto off32) {
+    constexpr int MZ = decltype(mz)::value;
+    constexpr bool O = decltype(off32)::value;
+    if (m.val == nullptr)
+      slq_spmm_kernel<true, MZ, O><<<plan.ngroups, kThreads, 0, s>>>(
+          m.rowptr, m.col, m.val, m.nrows, m.nnz, w, u, sdev, hub_rows(m), banded(m, plan), part);
     else
-      slq_spmm_kernel<false, MZ, TL><<<plan.ngroups, kThreads, 0, s>>>(
-          m.rowptr, m.col, m.val, m.nrows, m.nnz, w, u, sdev, hub, banded(m, plan), part);
+      slq_spmm_kernel<false, MZ, O><<<plan.ngroups, kThreads, 0, s>>>(
+          m.rowptr, m.col, m.val, m.nrows, m.nnz, w, u, sdev, hub_rows(m), banded(m, plan), part);
     return hipGetLastError();
   });
 }
@@ -1857,13 +2115,13 @@ hipError_t launch_csr_step_batched(hipStream_t s, const BatchBlock* tab, const i
                                    int maxnz, int zmode) {
   const bool hp = step > 1;
   const unsigned grid = (unsigned)groups;
-#define MLCT_BATCH(P, Z, H, M, T) \
-  csr_step_batched_kernel<P, Z, H, M, T><<<grid, kThreads, 0, s>>>(tab, xblk, xg0, xbase, xl, step)
-#define MLCT_BATCH_M(P, Z, H)                                                       \
-  if (maxnz <= 4) MLCT_BATCH(P, Z, H, 4, kTailNone);                                \
-  else if (maxnz <= 5) MLCT_BATCH(P, Z, H, 5, kTailNone);                           \
-  else if (maxnz <= 8) MLCT_BATCH(P, Z, H, 8, kTailNone);                           \
-  else MLCT_BATCH(P, Z, H, 8, kTailGen)
+#define MLCT_BATCH(P, Z, H, M) \
+  csr_step_batched_kernel<P, Z, H, M><<<grid, kThreads, 0, s>>>(tab, xblk, xg0, xbase, xl, step)
+#define MLCT_BATCH_M(P, Z, H)                  \
+  if (maxnz <= 4) MLCT_BATCH(P, Z, H, 4);      \
+  else if (maxnz <= 5) MLCT_BATCH(P, Z, H, 5); \
+  else if (maxnz <= 8) MLCT_BATCH(P, Z, H, 8); \
+  else MLCT_BATCH(P, Z, H, 0)
 #define MLCT_BATCH_H(P, Z) \
   if (hp) { MLCT_BATCH_M(P, Z, true); } else { MLCT_BATCH_M(P, Z, false); }
 #define MLCT_BATCH_Z(P) \
@@ -1898,14 +2156,14 @@ hipError_t launch_csr_batch_persistent(hipStream_t s, const BatchBlock* tab,
   pl.spin_ticks = spin_ticks;
   void* args[] = {(void*)&tab, (void*)&xblk, (void*)&xg0, (void*)&xbase, (void*)&pl};
   const dim3 grid((unsigned)(8 * per_xcd)), block(kThreads);
-#define MLCT_PERSIST(P, Z, M, T)                                                          \
-  return hipLaunchCooperativeKernel((const void*)csr_batch_persistent_kernel<P, Z, M, T>, \
+#define MLCT_PERSIST(P, Z, M)                                                          \
+  return hipLaunchCooperativeKernel((const void*)csr_batch_persistent_kernel<P, Z, M>, \
                                     grid, block, args, 0, s)
-#define MLCT_PERSIST_M(P, Z)                              \
-  if (maxnz <= 4) MLCT_PERSIST(P, Z, 4, kTailNone);       \
-  else if (maxnz <= 5) MLCT_PERSIST(P, Z, 5, kTailNone);  \
-  else if (maxnz <= 8) MLCT_PERSIST(P, Z, 8, kTailNone);  \
-  else MLCT_PERSIST(P, Z, 8, kTailGen)
+#define MLCT_PERSIST_M(P, Z)                  \
+  if (maxnz <= 4) MLCT_PERSIST(P, Z, 4);      \
+  else if (maxnz <= 5) MLCT_PERSIST(P, Z, 5); \
+  else if (maxnz <= 8) MLCT_PERSIST(P, Z, 8); \
+  else MLCT_PERSIST(P, Z, 0)
 #define MLCT_PERSIST_Z(P) \
   if (zmode == 0) { MLCT_PERSIST_M(P, 0); } else { MLCT_PERSIST_M(P, 1); }
   if (pattern) { MLCT_PERSIST_Z(true); } else { MLCT_PERSIST_Z(false); }
@@ -1917,14 +2175,14 @@ hipError_t launch_csr_batch_persistent(hipStream_t s, const BatchBlock* tab,
 int csr_batch_persistent_per_xcd(bool pattern, int maxnz, int zmode) {
   int per_cu = 0;
   hipError_t e = hipSuccess;
-#define MLCT_OCC(P, Z, M, T)                                                                \
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(                                         \
-      &per_cu, (const void*)csr_batch_persistent_kernel<P, Z, M, T>, kThreads, 0)
-#define MLCT_OCC_M(P, Z)                              \
-  if (maxnz <= 4) MLCT_OCC(P, Z, 4, kTailNone);       \
-  else if (maxnz <= 5) MLCT_OCC(P, Z, 5, kTailNone);  \
-  else if (maxnz <= 8) MLCT_OCC(P, Z, 8, kTailNone);  \
-  else MLCT_OCC(P, Z, 8, kTailGen)
+#define MLCT_OCC(P, Z, M)                           \
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor( \
+      &per_cu, (const void*)csr_batch_persistent_kernel<P, Z, M>, kThreads, 0)
+#define MLCT_OCC_M(P, Z)                  \
+  if (maxnz <= 4) MLCT_OCC(P, Z, 4);      \
+  else if (maxnz <= 5) MLCT_OCC(P, Z, 5); \
+  else if (maxnz <= 8) MLCT_OCC(P, Z, 8); \
+  else MLCT_OCC(P, Z, 0)
 #define MLCT_OCC_Z(P) \
   if (zmode == 0) { MLCT_OCC_M(P, 0); } else { MLCT_OCC_M(P, 1); }
   if (pattern) { MLCT_OCC_Z(true); } else { MLCT_OCC_Z(false); }
@@ -2008,17 +2266,17 @@ template hipError_t launch_probe_init<double>(hipStream_t, double*, int64_t, Pro
                                               const CsrStepPlan&, double*);
 template hipError_t launch_csr_step<float>(hipStream_t, const CsrMat&, const float*, float*,
                                            float, float, bool, int, ProbeSrc,
-                                           const CsrStepPlan&, void*, double*);
+                                           const CsrStepPlan&, double*);
 template hipError_t launch_csr_step<double>(hipStream_t, const CsrMat&, const double*,
                                             double*, double, double, bool, int, ProbeSrc,
-                                            const CsrStepPlan&, void*, double*);
+                                            const CsrStepPlan&, double*);
 template hipError_t launch_gram_csr_step<float>(hipStream_t, const CsrMat&, const CsrMat&,
                                                 const float*, float*, float*, float, float, bool,
                                                 int, ProbeSrc, const CsrStepPlan&,
-                                                const CsrStepPlan&, void*, void*, double*);
+                                                const CsrStepPlan&, double*);
 template hipError_t launch_gram_csr_step<double>(hipStream_t, const CsrMat&, const CsrMat&,
                                                  const double*, double*, double*, double, double,
                                                  bool, int, ProbeSrc, const CsrStepPlan&,
-                                                 const CsrStepPlan&, void*, void*, double*);
+                                                 const CsrStepPlan&, double*);
 
 }  // namespace mlct
