@@ -219,7 +219,9 @@ mlct_status mlct_set_option(mlct_ctx* ctx, int32_t option, int64_t value);
 typedef enum {
   MLCT_KERNEL_CSR_STEP = 0,   /* one recurrence step over a CSR operator   */
   MLCT_KERNEL_DENSE_STEP = 1, /* one recurrence step over a dense operator */
-  MLCT_KERNEL_TRI_STEP = 2,   /* one integer triangle-moment SpMM          */
+  MLCT_KERNEL_TRI_STEP = 2,   /* integer triangle-moment SpMMs; its count is
+                                 of products with 64 probes (up to 8 in one
+                                 launch)                                    */
   MLCT_KERNEL_GRAM = 3,       /* Gram matrix formation                     */
   MLCT_KERNEL_BATCH_STEP = 4, /* one batched recurrence step (all blocks)  */
   MLCT_KERNEL_GRAM_CSR_STEP = 5, /* one step over X^T X + lambda I, X CSR:

@@ -117,6 +117,17 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
   return MLCT_OK;
 }
 
+// Frees a workspace slot (the next ws_get allocates it again).
+mlct_status ws_drop(mlct_ctx* ctx, int slot) {
+  DevBuf& b = ctx->slots[slot];
+  if (!b.ptr) return MLCT_OK;
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  HIPCHK(ctx, hipFree(b.ptr));
+  ctx->ws_total -= b.bytes;
+  b = DevBuf{};
+  return MLCT_OK;
+}
+
 // ---- kernel timing --------------------------------------------------------
 hipEvent_t pool_event(mlct_ctx* ctx) {
   if (!ctx->event_pool.empty()) {
@@ -633,7 +644,7 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
   std::vector<int> order(n);
   for (int i = 0; i < n; ++i) order[i] = i;
   std::sort(order.begin(), order.end(), [&](int x, int y) { return h[3 * x] < h[3 * y]; });
-  std::vector<int32_t> rows(n), c0(n + 1), cs, ce;
+  std::vector<int32_t> rows(n), c0(n + 1), cs, ce, cr;
   for (int k = 0; k < n; ++k) {
     const int32_t* t = &h[3 * (size_t)order[k]];
     rows[k] = t[0];
@@ -641,11 +652,12 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
     for (int32_t a = t[1]; a < t[2]; a += kHubChunk) {
       cs.push_back(a);
       ce.push_back(std::min<int32_t>(a + kHubChunk, t[2]));
+      cr.push_back(t[0]);
     }
   }
   c0[n] = (int32_t)cs.size();
   const size_t nch = cs.size();
-  const size_t words = (size_t)n + (n + 1) + 2 * nch;
+  const size_t words = (size_t)n + (n + 1) + 3 * nch;
   void* mem = nullptr;
   if (hipMalloc(&mem, words * sizeof(int32_t)) != hipSuccess) {
     (void)hipGetLastError();
@@ -657,6 +669,7 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
   all.insert(all.end(), c0.begin(), c0.end());
   all.insert(all.end(), cs.begin(), cs.end());
   all.insert(all.end(), ce.begin(), ce.end());
+  all.insert(all.end(), cr.begin(), cr.end());
   const hipError_t e = hipMemcpy(mem, all.data(), words * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(mem);
@@ -668,6 +681,7 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
   mat.hub_c0 = base + n;
   mat.hub_cs = base + n + (n + 1);
   mat.hub_ce = mat.hub_cs + nch;
+  mat.hub_cr = mat.hub_ce + nch;
   mat.hub_n = n;
   mat.hub_chunks = (int)nch;
   return MLCT_OK;
@@ -1655,40 +1669,62 @@ mlct_status mlct_triangles(mlct_ctx* ctx, const mlct_op* op, int64_t m, uint64_t
     return fail(ctx, MLCT_EUNSUPPORTED, "triangle counting supports at most 536,870,911 rows");
   CHECK(set_device(ctx));
   const CsrStepPlan plan = plan_csr(op->d, op->tuned_groups);
+  // Panels of 64 probes per pass: up to 512 probes share the reading of the
+  // pattern in pass 1, while y (128 bytes per row and panel) stays within
+  // 1 GiB and the workspace allows it; one panel is the least.
+  constexpr int64_t kMaxY = (int64_t)1 << 30;
+  const int64_t ybytes = op->d * kBlockProbes * (int64_t)sizeof(int16_t);
+  int panels = (int)std::min<int64_t>(kTriPanels, (m + kBlockProbes - 1) / kBlockProbes);
+  panels = (int)std::max<int64_t>(1, std::min<int64_t>(panels, kMaxY / ybytes));
   void *z, *y, *part, *w, *res, *side = nullptr;
-  CHECK(ws_get(ctx, WS_V0, (size_t)op->d * sizeof(uint64_t), &z));        // packed signs
-  CHECK(ws_get(ctx, WS_V1, (size_t)op->d * kBlockProbes * sizeof(int16_t), &y));
-  if (op->csr.hub_n > 0)
-    CHECK(ws_get(ctx, WS_TRISIDE, (size_t)op->csr.hub_n * kBlockProbes * sizeof(int32_t), &side));
-  CHECK(ws_get(ctx, WS_PART, (size_t)2 * plan.ngroups * kBlockProbes * sizeof(long long), &part));
-  CHECK(ws_get(ctx, WS_TRI, (size_t)m * 3 * sizeof(long long), &w));
-  CHECK(ws_get(ctx, WS_RESULT, sizeof(mlct_tri_result), &res));
-  void* hub = nullptr;
-  if (op->csr.hub_n > 0)
-    CHECK(ws_get(ctx, WS_HUB, (size_t)op->csr.hub_chunks * kBlockProbes * sizeof(int32_t), &hub));
+  auto take = [&](int np) -> mlct_status {
+    CHECK(ws_get(ctx, WS_V0, (size_t)op->d * np * sizeof(uint64_t), &z));  // packed signs
+    CHECK(ws_get(ctx, WS_V1, (size_t)np * ybytes, &y));
+    if (op->csr.max_row_nnz > 32767)
+      CHECK(ws_get(ctx, WS_TRISIDE, (size_t)np * op->csr.hub_n * kBlockProbes * sizeof(int32_t),
+                   &side));
+    CHECK(ws_get(ctx, WS_PART, (size_t)plan.ngroups * sizeof(uint64_t), &part));
+    CHECK(ws_get(ctx, WS_TRI, (size_t)m * 3 * sizeof(long long), &w));
+    return ws_get(ctx, WS_RESULT, sizeof(mlct_tri_result), &res);
+  };
+  mlct_status got = take(panels);
+  if (got == MLCT_ENOMEM && panels > 1) {
+    // what the wide attempt took goes back before the narrow one
+    ctx->err.clear();
+    for (int slot : {WS_V0, WS_V1, WS_TRISIDE}) CHECK(ws_drop(ctx, slot));
+    panels = 1;
+    got = take(1);
+  }
+  CHECK(got);
   hipStream_t s = ctx->stream;
-  long long* P = static_cast<long long*>(part);
   long long* W = static_cast<long long*>(w);
-  for (int64_t p0 = 0; p0 < m; p0 += kBlockProbes) {
+  uint64_t* Z = static_cast<uint64_t*>(z);
+  int16_t* Y = static_cast<int16_t*>(y);
+  int32_t* S = static_cast<int32_t*>(side);
+  // until the result is written there: the symmetry word, the escapes word
+  uint64_t* asym = static_cast<uint64_t*>(res);
+  uint32_t* esc = reinterpret_cast<uint32_t*>(asym + 1);
+  HIPCHK(ctx, launch_tri_sym(s, op->csr, plan.ngroups, part, asym));
+  HIPCHK(ctx, launch_fill_zero_i32(s, static_cast<int*>(w), m * 6));
+  const int64_t group = (int64_t)panels * kBlockProbes;
+  for (int64_t p0 = 0; p0 < m; p0 += group) {
     ProbeSrc src{};
     src.seed = seed;
     src.first_id = p0;
-    src.active = (int32_t)((m - p0) < kBlockProbes ? (m - p0) : kBlockProbes);
-    HIPCHK(ctx, launch_tri_init(s, op, src, plan, static_cast<uint64_t*>(z)));
+    src.active = (int32_t)std::min<int64_t>(m - p0, group);
+    const int np = (src.active + kBlockProbes - 1) / kBlockProbes;
+    HIPCHK(ctx, launch_tri_init(s, op->d, src, np, Z, esc));
     {
       LaunchTimer tm(ctx, MLCT_KERNEL_TRI_STEP);
-      HIPCHK(ctx, launch_tri_step(s, op->csr, 1, plan, static_cast<uint64_t*>(z),
-                                  static_cast<int16_t*>(y), static_cast<int32_t*>(side), hub, P));
-      tm.done();
+      HIPCHK(ctx, launch_tri_pass1(s, op->csr, plan, Z, np, Y, S, esc));
+      tm.done(np);
     }
-    HIPCHK(ctx, launch_tri_reduce(s, P, plan.ngroups, src.active, 1, W, p0));
     {
       LaunchTimer tm(ctx, MLCT_KERNEL_TRI_STEP);
-      HIPCHK(ctx, launch_tri_step(s, op->csr, 2, plan, nullptr, static_cast<int16_t*>(y),
-                                  static_cast<int32_t*>(side), hub, P));
-      tm.done();
+      HIPCHK(ctx, launch_tri_pass2(s, op->csr, plan, np, Z, Y, S, asym, esc, src.active,
+                                   W + 3 * p0));
+      tm.done(np);
     }
-    HIPCHK(ctx, launch_tri_reduce(s, P, plan.ngroups, src.active, 2, W, p0));
   }
   HIPCHK(ctx, launch_tri_cv(s, W, m, op->csr.nnz, static_cast<mlct_tri_result*>(res)));
   mlct_tri_result h;
@@ -2339,8 +2375,7 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     B.ngroups = plan.ngroups;
     B.rows_per_group = plan.rows_per_group;
     B.band = op->csr.band && op->csr.band_groups == plan.ngroups ? op->csr.band : nullptr;
-    B.hubs = HubRows{op->csr.hub_rows, op->csr.hub_c0, op->csr.hub_cs, op->csr.hub_ce,
-                     op->csr.hub_n};
+    B.hubs = hub_rows(op->csr);
   }
   std::vector<double*> mu(nitems), coef(nitems), qst(nitems);
   for (int i = 0; i < nitems; ++i) {

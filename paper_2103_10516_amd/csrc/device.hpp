@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -71,6 +72,36 @@ __device__ __forceinline__ int read_lane<int>(int v, int l) {
 template <>
 __device__ __forceinline__ float read_lane<float>(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
+
+// Lane I of each row of 16 lanes, in all of them.
+template <int I>
+__device__ __forceinline__ int bcast16(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xf, 0xf, false);
+}
+
+// First hub row at or past row r, by a 64-way search over the wave's lanes
+// (two loads deep up to 4,096 rows; a binary search's chain of loads takes
+// longer than a short band).
+__device__ __forceinline__ int hub_lower(const HubRows& h, int64_t r) {
+  int lo = 0, hi = h.n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) / 64;
+    const int i = lo + lane_id() * step;
+    const int cnt = __popcll(__ballot(i < hi && h.rows[min(i, h.n - 1)] < r));
+    if (cnt == 0) break;
+    hi = min(hi, lo + cnt * step);
+    lo += (cnt - 1) * step + 1;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
 }
 
 }  // namespace mlct

@@ -37,6 +37,7 @@ struct CsrMat {
   int32_t* hub_c0 = nullptr;    // [hub_n + 1]
   int32_t* hub_cs = nullptr;    // [hub_chunks] first entry of each chunk
   int32_t* hub_ce = nullptr;    // [hub_chunks] one past its last entry
+  int32_t* hub_cr = nullptr;    // [hub_chunks] its row
   int hub_n = 0, hub_chunks = 0;
   // Row bands of equal work for matrices with very uneven rows (owned by the
   // operator): band[g] .. band[g + 1] - 1 are workgroup g's rows when a step
@@ -234,15 +235,25 @@ CsrStepPlan plan_csr(int64_t d, int max_groups = 0);
 template <typename T>
 hipError_t launch_probe_init(hipStream_t s, T* v0, int64_t d, ProbeSrc src,
                              const CsrStepPlan& plan, double* part0);
-// Rows longer than kHubLen: sorted row ids, the first chunk of each and each
-// chunk's entries [cs, ce).
+// Rows longer than kHubLen: sorted row ids, the first chunk of each, each
+// chunk's entries [cs, ce) and its row.
 struct HubRows {
   const int32_t* rows;
   const int32_t* c0;
   const int32_t* cs;
   const int32_t* ce;
+  const int32_t* cr;
   int n;
 };
+inline HubRows hub_rows(const CsrMat& m) {
+  return HubRows{m.hub_rows, m.hub_c0, m.hub_cs, m.hub_ce, m.hub_cr, m.hub_n};
+}
+// The plan with the matrix's equal-work row bands when they were built for
+// this number of workgroups, else with equal row counts.
+inline CsrStepPlan banded(const CsrMat& m, CsrStepPlan p) {
+  p.band = (m.band != nullptr && m.band_groups == p.ngroups) ? m.band : nullptr;
+  return p;
+}
 
 // One probe block of a batch (FP32, 64 probes) over one CSR operator.
 struct BatchBlock {
@@ -400,17 +411,25 @@ hipError_t launch_slq_combine(hipStream_t s, const double* mu, int64_t ldmu, con
                               double log_scale, mlct_result* out);
 
 // ---- integer triangle moments (k_tri.hip) ----------------------------------
-// z of a probe block packed one 64-bit word per row (bit p: probe p is -1).
-hipError_t launch_tri_init(hipStream_t s, const mlct_op* op, ProbeSrc src,
-                           const CsrStepPlan& plan, uint64_t* zbits);
-// Pass 1 gathers zbits and writes y = A z (int16 rows [d][64]; values past
-// +-32767 as -32768 with the exact value in side[hub slot][64]); pass 2
-// gathers y.  side: [hub_n][64] int32; hub_part: the hub chunk partials.
-hipError_t launch_tri_step(hipStream_t s, const CsrMat& m, int pass, const CsrStepPlan& plan,
-                           const uint64_t* zbits, int16_t* y, int32_t* side, void* hub_part,
-                           long long* part);
-hipError_t launch_tri_reduce(hipStream_t s, const long long* part, int ngroups, int active,
-                             int pass, long long* w, int64_t p0);
+// Groups of up to kTriPanels panels of 64 probes.  launch_tri_init: z, one
+// 64-bit sign word per row and panel, a row's panels side by side.
+// launch_tri_sym: *asym = 0 if the pattern is symmetric (part: ngroups words of
+// scratch).  Pass 1: y = A z (int16, [panel][d][64]; values past +-32767 as
+// -32768 with the exact value in side[panel][hub slot][64], needed with rows
+// longer than 32,767 only; *escapes, cleared by launch_tri_init, gets the bit
+// of each panel that has one); pass 2 adds w1, w2, w3 of the group's first
+// `active` probes to w (3 per probe).
+constexpr int kTriPanels = 8;
+hipError_t launch_tri_init(hipStream_t s, int64_t d, ProbeSrc src, int panels, uint64_t* zbits,
+                           uint32_t* escapes);
+hipError_t launch_tri_sym(hipStream_t s, const CsrMat& m, int ngroups, void* part, uint64_t* asym);
+hipError_t launch_tri_pass1(hipStream_t s, const CsrMat& m, const CsrStepPlan& plan,
+                            const uint64_t* zbits, int panels, int16_t* y, int32_t* side,
+                            uint32_t* escapes);
+hipError_t launch_tri_pass2(hipStream_t s, const CsrMat& m, const CsrStepPlan& plan, int panels,
+                            const uint64_t* zbits, const int16_t* y, int32_t* side,
+                            const uint64_t* asym, const uint32_t* escapes, int64_t active,
+                            long long* w);
 hipError_t launch_tri_cv(hipStream_t s, const long long* w, int64_t m, int64_t nnz,
                          mlct_tri_result* out);
 

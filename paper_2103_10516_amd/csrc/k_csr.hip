@@ -19,15 +19,10 @@
 // probes and a wave instruction moves several rows, with the same row sums,
 // update and moment summation order as the lane = probe body.
 //
-// The same row machinery runs the integer passes of triangle counting
-// (T = int32, pattern rows, int64 partials): only the per-row epilogue
-// differs, so it is a policy type (RecEpi, TriEpi).
-//
-// Long rows (more than kHubLen entries, the hubs of power-law graphs) would
-// leave one wave walking tens of thousands of gathers while the rest of the
-// device idles.  Their entries are cut into chunks of kHubChunk that a
-// separate launch (csr_hub_kernel) reduces first, one wave per chunk; the
-// step kernel then sums a hub row's chunk partials in chunk order.
+// Longer rows take a form whose lanes also hold 16 bytes of probes, one row
+// per group of lanes (long_band); rows past kHubLen, the hubs of power-law
+// graphs, would leave one wave walking tens of thousands of gathers, and are
+// cut into chunks of kHubChunk that the workgroup of their band shares.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -41,21 +36,16 @@ namespace {
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 
-// What a step kernel does with rows the straight-line path cannot take.
-constexpr int kTailNone = 0;  // nothing: no row is longer than MAXNZ
-constexpr int kTailGen = 1;   // the generic loop
-constexpr int kTailHubs = 2;  // the generic loop, and hub partials past kHubLen
-
-template <typename P>
-__device__ __forceinline__ void store_partials(P a1, P a2, int g, int ngroups,
-                                               P* __restrict__ part, int probe = lane_id()) {
-  __shared__ P sh[2][kWaves][64];
+__device__ __forceinline__ void store_partials(double a1, double a2, int g, int ngroups,
+                                               double* __restrict__ part,
+                                               int probe = lane_id()) {
+  __shared__ double sh[2][kWaves][64];
   const int lane = lane_id(), wave = wave_id();
   sh[0][wave][probe] = a1;
   sh[1][wave][probe] = a2;
   __syncthreads();
   if (wave == 0) {
-    P s1 = sh[0][0][lane], s2 = sh[1][0][lane];
+    double s1 = sh[0][0][lane], s2 = sh[1][0][lane];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) {
       s1 += sh[0][w][lane];
@@ -96,7 +86,7 @@ __device__ __forceinline__ void probe_init_wg(T* __restrict__ v0, int64_t d, con
     v0[i * 64 + lane] = z;
     acc += (double)z * (double)z;
   }
-  store_partials<double>(acc, 0.0, g, ngroups, part);
+  store_partials(acc, 0.0, g, ngroups, part);
 }
 
 template <typename T>
@@ -117,9 +107,6 @@ __global__ __launch_bounds__(kThreads) void probe_init_kernel(T* __restrict__ v0
 // quads take one class each, so both kernels give the same bits.
 template <typename T, int ZMODE, bool HAS_PREV, bool KEEP = false, int CLS = 1>
 struct RecEpi {
-  using Part = double;
-  static constexpr bool kOwn = true;    // needs V_k[i] of its own row
-  static constexpr bool kParts = true;  // writes moment partials
   static constexpr int kCls = (ZMODE <= 1 && sizeof(T) == 4) ? CLS : 1;
   T ca, cb;
   T* vm;
@@ -174,72 +161,13 @@ struct RecEpi {
   }
 };
 
-// The int16 form of y (triangle passes): a value outside [-32767, 32767]
-// is stored as this sentinel, its exact value in the row of its hub (rows
-// longer than kHubLen, the only ones that can hold such a value) in a side
-// table.
-constexpr int32_t kY16Sentinel = -32768;
-struct HubSide {
-  const int32_t* rows;  // sorted hub row ids
-  int n;
-  int32_t* side;        // [n][64] exact values of the sentinel entries
-  __device__ __forceinline__ int slot(int64_t i) const {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (rows[mid] < i) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-  }
-};
-
-// Per-row epilogue of the triangle passes (exact int64 sums):
-//   PASS 1: y = A z stored as int16 rows (a value beyond +-32767 as the
-//           sentinel, exact in the hub side table: see Y16Reader),
-//           slot 0 = z.y, slot 1 = y.y
-//   PASS 2: w = A y not stored, slot 0 = y.w.
-// |y_i| <= deg(i) and |w_i| <= nnz < 2^31, so int32 holds every sum.
-template <int PASS>
-struct TriEpi {
-  using Part = long long;
-  static constexpr bool kOwn = true;
-  static constexpr bool kParts = true;
-  int16_t* vout;
-  HubSide hs;
-  long long a1 = 0, a2 = 0;
-  __device__ TriEpi(int16_t* v, const HubSide& h) : vout(v), hs(h) {}
-  __device__ __forceinline__ int32_t prev(int64_t) const { return 0; }
-  __device__ __forceinline__ long long part1() const { return a1; }
-  __device__ __forceinline__ long long part2() const { return a2; }
-  __device__ __forceinline__ void finish(int64_t i, int32_t acc, int32_t own, int32_t, int) {
-    const int lane = lane_id();
-    if (PASS == 1) {
-      int16_t st = (int16_t)acc;
-      if (__builtin_expect(acc < -32767 || acc > 32767, 0)) {
-        st = (int16_t)kY16Sentinel;
-        hs.side[(int64_t)hs.slot(i) * 64 + lane] = acc;
-      }
-      __builtin_nontemporal_store(st, vout + i * 64 + lane);
-      a1 += (long long)own * acc;
-      a2 += (long long)acc * acc;
-    } else {
-      if (__builtin_expect(own == kY16Sentinel, 0)) own = hs.side[(int64_t)hs.slot(i) * 64 + lane];
-      a1 += (long long)own * acc;
-    }
-  }
-};
-
 // One gathered entry into a row sum: weight w (ignored for patterns) times x,
 // or nothing when on is false.
 template <typename T, bool PATTERN>
 __device__ __forceinline__ T accum(T acc, float w, bool on, T x) {
-  if constexpr (std::is_integral<T>::value) {
-    return acc + (on ? x : T(0));
-  } else {
-    const float onf = on ? 1.f : 0.f;
-    const float ww = PATTERN ? onf : w * onf;
-    return fma((T)ww, x, acc);
-  }
+  const float onf = on ? 1.f : 0.f;
+  const float ww = PATTERN ? onf : w * onf;
+  return fma((T)ww, x, acc);
 }
 
 // Gathers of block rows.  With OFF32 (block under 4 GiB, FP32) they are
@@ -249,8 +177,6 @@ __device__ __forceinline__ T accum(T acc, float w, bool on, T x) {
 // as 0 (the resource's size is the block's size).
 template <typename T, bool OFF32>
 struct RowReader {
-  using Elem = T;  // element type of the gathered block
-  using Val = T;   // type of a gathered value
   const T* base;
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t lane_off;
@@ -266,198 +192,12 @@ struct RowReader {
       static_assert(sizeof(T) == 4, "32-bit offsets are for 4-byte elements");
       const uint32_t bits = __builtin_amdgcn_raw_buffer_load_b32(
           rsrc, lane_off, (int)((uint32_t)j * (uint32_t)(64 * sizeof(T))), 0);
-      if constexpr (std::is_integral<T>::value) return (T)bits;
-      else return __uint_as_float(bits);
+      return __uint_as_float(bits);
     } else {
       return base[j * 64 + lane];
     }
   }
-  // a gathered value as the row sum takes it (the raw value here)
-  static constexpr bool kFix = false;
-  __device__ __forceinline__ T fix(int64_t, T x) const { return x; }
-  // gathers by a byte offset precomputed as column * kRowBytes (buffer form)
-  // (raw load, then conversion: the sequence form issues every load of a
-  // batch before it converts the first)
-  static constexpr bool kScaled = OFF32 && sizeof(T) == 4;
-  static constexpr uint32_t kRowBytes = 64 * sizeof(T);
-  using Raw = uint32_t;
-  __device__ __forceinline__ uint32_t raw(uint32_t soff) const {
-    if constexpr (kScaled) return __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_off, (int)soff, 0);
-    else return 0u;
-  }
-  __device__ __forceinline__ T cvt(uint32_t bits) const {
-    if constexpr (std::is_integral<T>::value) return (T)bits;
-    else return __uint_as_float(bits);
-  }
 };
-
-// Triangle pass 1 gathers only Rademacher signs: one 64-bit word per row,
-// bit p set where probe p is -1.  Every lane of a wave gathers the same row:
-// lanes 0-31 load its low 32 bits and lanes 32-63 its high 32 bits by a
-// vector buffer load from a scalar row offset (one 8-byte request; vector
-// loads keep many more gathers in flight than scalar loads would).
-struct SignBitsReader {
-  using Elem = uint64_t;
-  using Val = int32_t;
-  __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t half_off;
-  int shift;
-  __device__ __forceinline__ SignBitsReader(const uint64_t* b, int64_t d, int lane) {
-    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t*>(b), (short)0,
-                                             (int)(uint32_t)(d * sizeof(uint64_t)), 0x00020000);
-    half_off = (uint32_t)(lane >> 5) * 4;
-    shift = lane & 31;
-  }
-  __device__ __forceinline__ int32_t operator()(int64_t j, int) const {
-    return cvt(raw((uint32_t)j * (uint32_t)sizeof(uint64_t)));
-  }
-  static constexpr bool kScaled = true;
-  static constexpr uint32_t kRowBytes = sizeof(uint64_t);
-  using Raw = uint32_t;
-  __device__ __forceinline__ uint32_t raw(uint32_t soff) const {
-    return __builtin_amdgcn_raw_buffer_load_b32(rsrc, half_off, (int)soff, 0);
-  }
-  __device__ __forceinline__ int32_t cvt(uint32_t w) const {
-    return 1 - 2 * (int32_t)__builtin_amdgcn_ubfe(w, (uint32_t)shift, 1u);
-  }
-  static constexpr bool kFix = false;
-  __device__ __forceinline__ int32_t fix(int64_t, int32_t x) const { return x; }
-};
-
-// Rows of 64 int16 values (triangle pass 2 gathers y = A z, |y_i| <= the
-// degree of row i).  A value outside [-32767, 32767], possible only on rows
-// longer than kHubLen (the hub rows), is stored as the sentinel -32768 with
-// the exact int32 value in that hub's row of a side table; fix() takes it
-// from there.  It is applied when the value is summed, after every gather
-// of the group was issued, so the check does not stall the gathers.
-template <bool OFF32>
-struct Y16Reader {
-  using Elem = int16_t;
-  using Val = int32_t;
-  const int16_t* base;
-  __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t lane_off;
-  HubSide hs;
-  __device__ __forceinline__ Y16Reader(const int16_t* y, int64_t d, int lane, const HubSide& h)
-      : base(y), hs(h) {
-    if (OFF32) {
-      rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int16_t*>(y), (short)0,
-                                               (int)(uint32_t)(d * 64 * sizeof(int16_t)),
-                                               0x00020000);
-      lane_off = (uint32_t)lane * sizeof(int16_t);
-    }
-  }
-  __device__ __forceinline__ int32_t operator()(int64_t j, int lane) const {
-    if constexpr (OFF32) {
-      return cvt(raw((uint32_t)j * kRowBytes));
-    } else {
-      return base[j * 64 + lane];
-    }
-  }
-  static constexpr bool kScaled = OFF32;
-  static constexpr uint32_t kRowBytes = 64 * sizeof(int16_t);
-  using Raw = uint16_t;
-  __device__ __forceinline__ uint16_t raw(uint32_t soff) const {
-    if constexpr (OFF32) return __builtin_amdgcn_raw_buffer_load_b16(rsrc, lane_off, (int)soff, 0);
-    else return 0;
-  }
-  __device__ __forceinline__ int32_t cvt(uint16_t bits) const { return (int32_t)(int16_t)bits; }
-  static constexpr bool kFix = true;
-  __device__ __forceinline__ int32_t fix(int64_t j, int32_t x) const {
-    if (__builtin_expect(x == kY16Sentinel, 0)) x = hs.side[(int64_t)hs.slot(j) * 64 + lane_id()];
-    return x;
-  }
-};
-
-// Applies rd.fix to n gathered values (x[u] from column col(u)) with one
-// test per batch: the sentinel is the smallest int16, so a batch holds one
-// only if its minimum equals it (rare: only hub rows' extreme sums).
-template <class RD, int N, class X, class C>
-__device__ __forceinline__ void fix_batch(const RD& rd, X* x, C col) {
-  if constexpr (RD::kFix) {
-    int32_t m = x[0];
-#pragma unroll
-    for (int u = 1; u < N; ++u) m = min(m, (int32_t)x[u]);
-    if (__builtin_expect(m == kY16Sentinel, 0)) {
-#pragma unroll
-      for (int u = 0; u < N; ++u) x[u] = rd.fix(col(u), x[u]);
-    }
-  }
-}
-
-// Generic row: 64-entry chunks of the row's columns, each loaded in one
-// coalesced read, then gathered 16 at a time (all 16 in flight before the
-// first is consumed; slots past the end gather the chunk's last row with
-// weight 0).
-constexpr int kGen = 16;
-// Gathers in flight per wave in the sequence form of a group (below).  16
-// for FP32 lowers the batched kernel's registers to four waves per SIMD but
-// measured 3x slower on the 64-graph Chung-Lu batch (more workgroups in
-// flight over a multi-GB gather working set); single-matrix steps time the
-// same with either.
-template <typename T>
-constexpr int kFlatOf = sizeof(T) == 8 ? 16 : 32;
-
-template <typename T, bool PATTERN, class RD>
-__device__ __forceinline__ T row_dot_generic(const int32_t* __restrict__ col,
-                                             const float* __restrict__ val, const RD& rd,
-                                             int64_t s, int64_t e) {
-  const int lane = lane_id();
-  T acc = T(0);
-  for (int64_t base = s; base < e; base += 64) {
-    const int c = (int)min<int64_t>(64, e - base);
-    const int64_t ce = base + min(lane, c - 1);
-    const int cj = col[ce];
-    const float av = PATTERN ? 1.f : val[ce];
-    for (int t = 0; t < c; t += kGen) {
-      T x[kGen];
-#pragma unroll
-      for (int u = 0; u < kGen; ++u) x[u] = rd(read_lane(cj, min(t + u, c - 1)), lane);
-      fix_batch<RD, kGen>(rd, x, [&](int u) { return read_lane(cj, min(t + u, c - 1)); });
-#pragma unroll
-      for (int u = 0; u < kGen; ++u)
-        acc = accum<T, PATTERN>(acc, PATTERN ? 1.f : read_lane(av, min(t + u, c - 1)),
-                                t + u < c, x[u]);
-    }
-  }
-  return acc;
-}
-
-// A row as consecutive chunks of kHubChunk entries, each reduced on its own
-// and the chunk sums added in order: the association the hub path uses, so a
-// row's sum is bitwise the same whether or not its chunks ran as a hub.
-template <typename T, bool PATTERN, class RD>
-__device__ __forceinline__ T row_dot_chunked(const int32_t* __restrict__ col,
-                                             const float* __restrict__ val, const RD& rd,
-                                             int64_t s, int64_t e) {
-  T acc = T(0);
-  for (int64_t c0 = s; c0 < e; c0 += kHubChunk)
-    acc += row_dot_generic<T, PATTERN>(col, val, rd, c0, min<int64_t>(c0 + kHubChunk, e));
-  return acc;
-}
-
-// Hub rows: sorted row ids, the first chunk of each (hub_c0[k] .. hub_c0[k+1]),
-// and the chunk partials of the current step (chunk-major, 64 lanes each).
-struct HubView {
-  const int32_t* rows;
-  const int32_t* c0;
-  int n;
-  const void* part;
-};
-
-template <typename T>
-__device__ __forceinline__ T hub_sum(const HubView& h, int64_t i) {
-  int lo = 0, hi = h.n - 1;  // the row is in the table
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (h.rows[mid] < i) lo = mid + 1; else hi = mid;
-  }
-  const int c0 = h.c0[lo], c1 = h.c0[lo + 1];
-  const T* p = static_cast<const T*>(h.part);
-  T acc = T(0);
-  for (int c = c0; c < c1; ++c) acc += p[(int64_t)c * 64 + lane_id()];
-  return acc;
-}
 
 // Extent of one group of up to ROWS consecutive rows.  The group's rows sit
 // in lanes q .. q+ROWS-1 of a batch: rs = start of the row's columns,
@@ -492,29 +232,17 @@ __device__ __forceinline__ GroupExt<ROWS> group_extent(int rs, int rlen, int q, 
 // the band side by side.  A wave fetches the row extents of its next 64/ROWS
 // groups in one load (a "batch", prefetched one batch ahead) and the column
 // indices and values of a group in one coalesced load, issued while the
-// previous group's gathers are in flight.  When every row of a group has at
-// most MAXNZ entries its gathers are straight-line code (unused slots gather
-// some valid row with weight 0), all in flight before the first is consumed.
-// Other groups (TAIL kTailGen / kTailHubs) are gathered as one sequence of
-// entries when no row exceeds kHubChunk, else row by row, rows longer than
-// kHubLen through their chunk partials (kTailHubs).  With kTailNone the
-// caller guarantees that no row is longer than MAXNZ (and ROWS * MAXNZ <=
-// 64), so every group is straight-line.
-//
-// d: rows processed; dv: rows of the gathered block vk.  SEP: the own-row
-// value V_k[i] the epilogue needs comes from vown instead of vk (the second
-// product of a Gram step gathers from W but recurs on V_k).
-template <typename T, bool PATTERN, int MAXNZ, bool OFF32, int TAIL, bool SEP, class Epi,
-          class RD = RowReader<T, OFF32>>
+// previous group's gathers are in flight.  No row is longer than MAXNZ (and
+// ROWS * MAXNZ <= 64), so a group's gathers are straight-line code (unused
+// slots gather some valid row with weight 0), all in flight before the first
+// is consumed.
+template <typename T, bool PATTERN, int MAXNZ, bool OFF32, class Epi>
 __device__ __forceinline__ void csr_step_wg(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const float* __restrict__ val, int64_t d, int64_t dv, int64_t nnz, const RD& rd,
-    const T* __restrict__ vown, Epi& epi, const HubView& hub, const CsrStepPlan& plan,
-    typename Epi::Part* __restrict__ part, int bid) {
+    const float* __restrict__ val, int64_t d, int64_t nnz, const RowReader<T, OFF32>& rd,
+    Epi& epi, const CsrStepPlan& plan, double* __restrict__ part, int bid) {
   constexpr int ROWS = MAXNZ <= 5 ? 8 : 4;
   constexpr int GPB = 64 / ROWS;  // groups per batch
-  constexpr bool HUBS = TAIL == kTailHubs;
-  constexpr int kFlat = kFlatOf<T>;
   const int lane = lane_id(), wave = wave_id();
   const int ngroups = plan.ngroups;
   const int g = xcd_band(bid, ngroups);
@@ -524,11 +252,6 @@ __device__ __forceinline__ void csr_step_wg(
 
   const int64_t ngrp = r1 > r0 ? (r1 - r0 + ROWS - 1) / ROWS : 0;  // groups in the band
   const int64_t nk = ngrp > wave ? (ngrp - wave + kWaves - 1) / kWaves : 0;  // this wave's
-  auto own = [&](int64_t i) -> T {
-    if constexpr (!Epi::kOwn) return T(0);
-    else if constexpr (SEP) return vown[i * 64 + lane];
-    else return rd(i, lane);
-  };
   // first row of this wave's k-th group, and its number of rows
   auto grp_row0 = [&](int64_t k) { return r0 + (k * kWaves + wave) * ROWS; };
   auto grp_rows = [&](int64_t k) { return (int)min<int64_t>(ROWS, r1 - grp_row0(k)); };
@@ -556,24 +279,20 @@ __device__ __forceinline__ void csr_step_wg(
     GroupExt<ROWS> cur = group_extent<ROWS>(rs, rlen, 0, grp_rows(0));
     int cj = 0;
     float av = 0.f;
-    if (nnz > 0) load_cols(cur, cj, av);
+    load_cols(cur, cj, av);
 
     while (true) {
       const int64_t row0 = grp_row0(k);
-      const bool fast =
-          TAIL == kTailNone || (nnz > 0 && cur.maxlen <= MAXNZ && cur.cnt <= 64);
-      T x[ROWS][MAXNZ > 0 ? MAXNZ : 1];
+      T x[ROWS][MAXNZ];
       T xi[ROWS], xp[ROWS];
-      if (fast) {
-        // all gathers of the group before anything else is issued
+      // all gathers of the group before anything else is issued
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-          const int64_t i = row0 + min(r, cur.nr - 1);
+      for (int r = 0; r < ROWS; ++r) {
+        const int64_t i = row0 + min(r, cur.nr - 1);
 #pragma unroll
-          for (int t = 0; t < MAXNZ; ++t) x[r][t] = rd(read_lane(cj, min(cur.off[r] + t, 63)), lane);
-          xi[r] = own(i);
-          xp[r] = epi.prev(i);
-        }
+        for (int t = 0; t < MAXNZ; ++t) x[r][t] = rd(read_lane(cj, min(cur.off[r] + t, 63)), lane);
+        xi[r] = rd(i, lane);
+        xp[r] = epi.prev(i);
       }
       // next group: extent and column prefetch
       const int64_t kn = k + 1;
@@ -586,132 +305,16 @@ __device__ __forceinline__ void csr_step_wg(
         const int qn = (int)(kn % GPB) * ROWS;
         nxt = new_batch ? group_extent<ROWS>(rs_n, rlen_n, 0, grp_rows(kn))
                         : group_extent<ROWS>(rs, rlen, qn, grp_rows(kn));
-        if (nnz > 0) load_cols(nxt, cjn, avn);
+        load_cols(nxt, cjn, avn);
       }
-      if (fast) {
-        if constexpr (RD::kFix) {
 #pragma unroll
-          for (int r = 0; r < ROWS; ++r)
-            fix_batch<RD, (MAXNZ > 0 ? MAXNZ : 1)>(
-                rd, x[r], [&](int t) { return read_lane(cj, min(cur.off[r] + t, 63)); });
-        }
+      for (int r = 0; r < ROWS; ++r) {
+        T acc = T(0);
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-          T acc = T(0);
-#pragma unroll
-          for (int t = 0; t < MAXNZ; ++t)
-            acc = accum<T, PATTERN>(acc, PATTERN ? 1.f : read_lane(av, min(cur.off[r] + t, 63)),
-                                    t < cur.len[r], x[r][t]);
-          if (r < cur.nr) epi.finish(row0 + r, acc, xi[r], xp[r], r);
-        }
-      } else if constexpr (TAIL != kTailNone) {
-        if (cur.maxlen <= kHubChunk) {
-          // the group's entries as one sequence: 64-entry chunks of column
-          // indices (the first already loaded), gathered kFlat at a time and
-          // summed in column order into a running sum that is handed to its
-          // row's accumulator at the row's last entry (rows are contiguous)
-          T acc[ROWS];
-#pragma unroll
-          for (int r = 0; r < ROWS; ++r) {
-            const int64_t i = row0 + min(r, cur.nr - 1);
-            acc[r] = T(0);
-            xi[r] = own(i);
-            xp[r] = epi.prev(i);
-          }
-          // per-group tables in lanes 0 .. ROWS: the position of row r's
-          // last entry (INT_MAX past the rows, so it is never reached) and
-          // the next row after r that has entries (ROWS: none); the current
-          // row rc and its end rend are uniform
-          int end_v = INT_MAX, nxt_v = ROWS;
-          int first = ROWS;
-#pragma unroll
-          for (int r = ROWS - 1; r >= 0; --r) {
-            if (lane == r) {
-              end_v = cur.len[r] > 0 ? cur.off[r] + cur.len[r] - 1 : INT_MAX;
-              nxt_v = first;
-            }
-            if (cur.len[r] > 0) first = r;
-          }
-          int rc = first;
-          int rend = read_lane(end_v, rc);
-          T run = T(0);
-          for (int base = 0; base < cur.cnt; base += 64) {
-            int cjc = cj;
-            float avc = av;
-            if (base > 0) {
-              const int64_t ce = min<int64_t>((int64_t)cur.gs + base + lane, nnz - 1);
-              cjc = col[ce];
-              avc = PATTERN ? 1.f : val[ce];
-            }
-            const int c = min(64, cur.cnt - base);
-            // lanes past the chunk's end repeat its last column (a valid row,
-            // not summed), and the reader's row offsets are formed once per
-            // chunk, so a gather is one lane read and one load
-            const int cl = lane < c ? cjc : read_lane(cjc, c - 1);
-            const int off = (int)((uint32_t)cl * RD::kRowBytes);
-#pragma unroll
-            for (int h = 0; h < 64 / kFlat; ++h) {
-              const int t = h * kFlat;
-              if (t >= c) break;
-              T xg[kFlat];
-              if constexpr (RD::kScaled) {
-                typename RD::Raw xr[kFlat];
-#pragma unroll
-                for (int u = 0; u < kFlat; ++u) xr[u] = rd.raw((uint32_t)read_lane(off, t + u));
-                // every load of the batch is in flight before the first is used
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int u = 0; u < kFlat; ++u) xg[u] = rd.cvt(xr[u]);
-              } else {
-#pragma unroll
-                for (int u = 0; u < kFlat; ++u) xg[u] = rd(read_lane(cl, t + u), lane);
-              }
-              fix_batch<RD, kFlat>(rd, xg, [&](int u) { return read_lane(cl, t + u); });
-              const int lim = c - t;         // entries of this batch in the group
-              int rloc = rend - (base + t);  // batch position of the current row's end
-              // summed in column order; at a row's last entry its sum goes to
-              // the row's accumulator and the next row begins
-              auto sum_batch = [&](auto full) {
-#pragma unroll
-                for (int u = 0; u < kFlat; ++u) {
-                  if (!decltype(full)::value && u >= lim) break;
-                  const float w = PATTERN ? 1.f : read_lane(avc, t + u);
-                  run = accum<T, PATTERN>(run, w, true, xg[u]);
-                  if (u == rloc) {
-#pragma unroll
-                    for (int r = 0; r < ROWS; ++r)
-                      if (r == rc) acc[r] = run;
-                    run = T(0);
-                    rc = read_lane(nxt_v, rc);
-                    rend = read_lane(end_v, rc);
-                    rloc = rend - (base + t);
-                  }
-                }
-              };
-              if (lim >= kFlat)
-                sum_batch(std::true_type());
-              else
-                sum_batch(std::false_type());
-            }
-          }
-#pragma unroll
-          for (int r = 0; r < ROWS; ++r)
-            if (r < cur.nr) epi.finish(row0 + r, acc[r], xi[r], xp[r], r);
-        } else {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {  // static indices: cur stays in registers
-          if (r < cur.nr) {
-            const int64_t i = row0 + r;
-            const int64_t s0 = (int64_t)cur.gs + cur.off[r];
-            T acc;
-            if (HUBS && cur.len[r] > kHubLen)
-              acc = hub_sum<T>(hub, i);
-            else
-              acc = row_dot_chunked<T, PATTERN>(col, val, rd, s0, s0 + cur.len[r]);
-            epi.finish(i, acc, own(i), epi.prev(i), r);
-          }
-        }
-        }
+        for (int t = 0; t < MAXNZ; ++t)
+          acc = accum<T, PATTERN>(acc, PATTERN ? 1.f : read_lane(av, min(cur.off[r] + t, 63)),
+                                  t < cur.len[r], x[r][t]);
+        if (r < cur.nr) epi.finish(row0 + r, acc, xi[r], xp[r], r);
       }
       if (!has_next) break;
       if (new_batch) {
@@ -726,8 +329,7 @@ __device__ __forceinline__ void csr_step_wg(
       av = avn;
     }
   }
-  if constexpr (Epi::kParts)
-    store_partials<typename Epi::Part>(epi.part1(), epi.part2(), g, ngroups, part);
+  store_partials(epi.part1(), epi.part2(), g, ngroups, part);
 }
 
 template <typename T, bool PATTERN, int ZMODE, bool HAS_PREV, int MAXNZ, bool OFF32>
@@ -736,10 +338,9 @@ __global__ __launch_bounds__(kThreads) void csr_step_kernel(
     const float* __restrict__ val, int64_t d, int64_t nnz, const T* __restrict__ vk,
     T* __restrict__ vm, T ca, T cb, ProbeSrc src, CsrStepPlan plan, double* __restrict__ part) {
   RecEpi<T, ZMODE, HAS_PREV, false, 4> epi(ca, cb, vm, src);
-  const HubView nohub{nullptr, nullptr, 0, nullptr};
-  csr_step_wg<T, PATTERN, MAXNZ, OFF32, kTailNone, false>(
-      rowptr, col, val, d, d, nnz, RowReader<T, OFF32>(vk, d, lane_id()), nullptr, epi, nohub, plan,
-      part, blockIdx.x);
+  csr_step_wg<T, PATTERN, MAXNZ, OFF32>(rowptr, col, val, d, nnz,
+                                        RowReader<T, OFF32>(vk, d, lane_id()), epi, plan, part,
+                                        blockIdx.x);
 }
 
 // ---- wide form of the step ------------------------------------------------------
@@ -1087,36 +688,6 @@ csr_step_wide_kernel(
 // 65,536 vertices 176 -> 75 ms.
 enum { kOpRec = 0, kOpStore = 1, kOpSlq = 2 };
 
-// First hub row at or past row r, by a 64-way search over the wave's lanes
-// (two loads deep up to 4,096 rows; a binary search's chain of loads takes
-// longer than a short band).
-__device__ __forceinline__ int hub_lower(const HubRows& h, int64_t r) {
-  int lo = 0, hi = h.n;
-  while (lo < hi) {
-    const int step = (hi - lo + 63) / 64;
-    const int i = lo + lane_id() * step;
-    const int cnt = __popcll(__ballot(i < hi && h.rows[min(i, h.n - 1)] < r));
-    if (cnt == 0) break;
-    hi = min(hi, lo + cnt * step);
-    lo += (cnt - 1) * step + 1;
-  }
-  return __builtin_amdgcn_readfirstlane(lo);
-}
-
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (N > 0) {
-    static_for<N - 1>(f);
-    f(std::integral_constant<int, N - 1>());
-  }
-}
-
-// Lane I of each row of 16 lanes, in all of them.
-template <int I>
-__device__ __forceinline__ int bcast16(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xf, 0xf, false);
-}
-
 // The slots' PPL x PPL exchange: element e of slot q goes to slot e, element q
 // (a lane had PPL probes of its slot's row, and has one probe of PPL rows).
 __device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
@@ -1407,7 +978,7 @@ __device__ __forceinline__ void long_band(
     }
   }
   if constexpr (OP != kOpStore)
-    store_partials<double>(m1, m2, g, plan.ngroups, part, probe);
+    store_partials(m1, m2, g, plan.ngroups, part, probe);
 }
 
 // (at least 4 waves per SIMD, two workgroups per CU)
@@ -1464,45 +1035,6 @@ __global__ __launch_bounds__(kThreads) void slq_spmm_kernel(
     long_band<double, PATTERN, 0, false, OFF32, kOpSlq>(rowptr, col, val, d, d, w, w, u, 0.0, 0.0,
                                                         ProbeSrc{}, hubs, 2, plan, part, g, sdev);
   }
-}
-
-// Integer pass of triangle counting over a pattern CSR: PASS 1 gathers the
-// packed signs of z (y = A z written to yout), PASS 2 gathers y (int16).
-template <int PASS, int MAXNZ, int TAIL, bool OFF32>
-__global__ __launch_bounds__(kThreads) void tri_step_kernel(
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col, int64_t d, int64_t nnz,
-    const uint64_t* __restrict__ zbits, const int16_t* __restrict__ yin,
-    int16_t* __restrict__ yout, HubSide hs, HubView hub, CsrStepPlan plan,
-    long long* __restrict__ part) {
-  TriEpi<PASS> epi(yout, hs);
-  if constexpr (PASS == 1)
-    csr_step_wg<int32_t, true, MAXNZ, false, TAIL, false>(
-        rowptr, col, nullptr, d, d, nnz, SignBitsReader(zbits, d, lane_id()), nullptr, epi, hub,
-        plan, part, blockIdx.x);
-  else
-    csr_step_wg<int32_t, true, MAXNZ, false, TAIL, false>(
-        rowptr, col, nullptr, d, d, nnz, Y16Reader<OFF32>(yin, d, lane_id(), hs), nullptr, epi,
-        hub, plan, part, blockIdx.x);
-}
-
-// Chunk partials of the hub rows for the triangle passes (as csr_hub_kernel).
-template <int PASS, bool OFF32>
-__global__ __launch_bounds__(256) void tri_hub_kernel(const int32_t* __restrict__ col, int64_t d,
-                                                      const uint64_t* __restrict__ zbits,
-                                                      const int16_t* __restrict__ yin,
-                                                      HubSide hs, const int32_t* __restrict__ cs,
-                                                      const int32_t* __restrict__ ce,
-                                                      int nchunks, int32_t* __restrict__ out) {
-  const int c = blockIdx.x * 4 + wave_id();
-  if (c >= nchunks) return;
-  const int lane = lane_id();
-  int32_t v;
-  if constexpr (PASS == 1)
-    v = row_dot_generic<int32_t, true>(col, nullptr, SignBitsReader(zbits, d, lane), cs[c], ce[c]);
-  else
-    v = row_dot_generic<int32_t, true>(col, nullptr, Y16Reader<OFF32>(yin, d, lane, hs), cs[c],
-                                       ce[c]);
-  out[(int64_t)c * 64 + lane] = v;
 }
 
 // Equal-work row bands by binary search on rowptr[r] + kBandRowCost * r.
@@ -1700,22 +1232,11 @@ __global__ __launch_bounds__(kThreads) void probe_init_batched_kernel(
   probe_init_wg<float>(B.v0, B.d, B.src, B.rows_per_group, B.ngroups, B.part, bid);
 }
 
-// The plan with the matrix's equal-work row bands when they were built for
-// this number of workgroups, else with equal row counts.
-CsrStepPlan banded(const CsrMat& m, CsrStepPlan p) {
-  p.band = (m.band != nullptr && m.band_groups == p.ngroups) ? m.band : nullptr;
-  return p;
-}
-
 // Whether gathers from a block of dv rows can use 32-bit offsets (block under
 // 4 GiB).
 template <typename T>
 bool block_off32(int64_t dv) {
   return (uint64_t)dv * 64 * sizeof(T) <= 0xFFFFFFFFull;
-}
-
-HubRows hub_rows(const CsrMat& m) {
-  return HubRows{m.hub_rows, m.hub_c0, m.hub_cs, m.hub_ce, m.hub_n};
 }
 
 // Row capacity of the straight-line path: the smallest of {4, 5, 8} that
@@ -1788,24 +1309,6 @@ hipError_t launch_step_any(hipStream_t s, const CsrMat& m, const T* vk, T* vm, T
   if (zmode == 0) return launch_step_nz<T, false, 0>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
   if (zmode == 1) return launch_step_nz<T, false, 1>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
   return launch_step_nz<T, false, 2>(s, m, vk, vm, ca, cb, has_prev, src, plan, part);
-}
-
-template <int PASS, bool OFF32>
-hipError_t launch_tri_pass(hipStream_t s, const CsrMat& m, const CsrStepPlan& plan,
-                           const uint64_t* zbits, const int16_t* yin, int16_t* yout,
-                           const HubSide& hs, const HubView& hub, long long* part) {
-  const dim3 grid(plan.ngroups), block(kThreads);
-#define MLCT_TRI(M, H)                                                                      \
-  tri_step_kernel<PASS, M, H, OFF32><<<grid, block, 0, s>>>(m.rowptr, m.col, m.nrows, m.nnz, \
-                                                            zbits, yin, yout, hs, hub,      \
-                                                            banded(m, plan), part)
-  if (m.hub_n > 0) MLCT_TRI(8, kTailHubs);
-  else if (m.nnz > 0 && m.max_row_nnz <= 4) MLCT_TRI(4, kTailNone);
-  else if (m.nnz > 0 && m.max_row_nnz <= 5) MLCT_TRI(5, kTailNone);
-  else if (m.nnz > 0 && m.max_row_nnz <= 8) MLCT_TRI(8, kTailNone);
-  else MLCT_TRI(8, kTailGen);
-#undef MLCT_TRI
-  return hipGetLastError();
 }
 
 // The two products of a Gram step for one pattern/valued and z-mode choice.
@@ -1953,7 +1456,6 @@ __global__ __launch_bounds__(kThreads) void csr_fused2_kernel(Fused2Args a) {
   plan.ngroups = a.ntiles;
   plan.rows_per_group = a.rows_per_tile;
   plan.band = nullptr;
-  const HubView hub{nullptr, nullptr, 0, nullptr};
   // Thread 0 sets the flag of the sub-step-1 tile just done and claims the
   // next ticket in one block at the loop head, and the ticket is made
   // wave-uniform: the loop's control flow is then uniform, so no lane of
@@ -1981,9 +1483,9 @@ __global__ __launch_bounds__(kThreads) void csr_fused2_kernel(Fused2Args a) {
     const int bid = t * 8 + xcd;  // the workgroup index whose band is tile base + t
     if (sub == 1) {
       RecEpi<float, Z1, PREV1, true, 4> epi(a.ca1, a.cb1, a.x, a.src);
-      csr_step_wg<float, PATTERN, MAXNZ, OFF32, kTailNone, false>(
-          a.rowptr, a.col, a.val, a.d, a.d, a.nnz, RowReader<float, OFF32>(a.y, a.d, lane_id()),
-          nullptr, epi, hub, plan, a.part1, bid);
+      csr_step_wg<float, PATTERN, MAXNZ, OFF32>(a.rowptr, a.col, a.val, a.d, a.nnz,
+                                                RowReader<float, OFF32>(a.y, a.d, lane_id()), epi,
+                                                plan, a.part1, bid);
       // every wave's stores complete (in L2) before the flag is set
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -1995,9 +1497,9 @@ __global__ __launch_bounds__(kThreads) void csr_fused2_kernel(Fused2Args a) {
       const int t0 = max(0, tile - w), t1 = min(a.ntiles - 1, tile + w);
       if (!fused_wait(a, t0, t1, t0 < base || t1 >= base + per)) break;
       RecEpi<float, Z2, true, false, 4> epi(a.ca2, a.cb2, a.y, a.src);
-      csr_step_wg<float, PATTERN, MAXNZ, OFF32, kTailNone, false>(
-          a.rowptr, a.col, a.val, a.d, a.d, a.nnz, RowReader<float, OFF32>(a.x, a.d, lane_id()),
-          nullptr, epi, hub, plan, a.part2, bid);
+      csr_step_wg<float, PATTERN, MAXNZ, OFF32>(a.rowptr, a.col, a.val, a.d, a.nnz,
+                                                RowReader<float, OFF32>(a.x, a.d, lane_id()), epi,
+                                                plan, a.part2, bid);
     }
   }
 }
@@ -2049,30 +1551,6 @@ hipError_t launch_gram_csr_step(hipStream_t s, const CsrMat& X, const CsrMat& XT
   if (zmode == 1) MLCT_GZ(false, 1);
   MLCT_GZ(false, 2);
 #undef MLCT_GZ
-}
-
-hipError_t launch_tri_step(hipStream_t s, const CsrMat& m, int pass, const CsrStepPlan& plan,
-                           const uint64_t* zbits, int16_t* y, int32_t* side, void* hub_part,
-                           long long* part) {
-  const HubView hub{m.hub_rows, m.hub_c0, m.hub_n, hub_part};
-  const HubSide hs{m.hub_rows, m.hub_n, side};
-  const bool off32 = (uint64_t)m.ncols * 64 * sizeof(int16_t) <= 0xFFFFFFFFull;
-  if (m.hub_n > 0) {
-    const int grid = (m.hub_chunks + 3) / 4;
-    int32_t* out = static_cast<int32_t*>(hub_part);
-#define MLCT_TH(P, O)                                                                          \
-  tri_hub_kernel<P, O><<<grid, 256, 0, s>>>(m.col, m.ncols, zbits, y, hs, m.hub_cs, m.hub_ce, \
-                                            m.hub_chunks, out)
-    if (pass == 1) MLCT_TH(1, true);
-    else if (off32) MLCT_TH(2, true);
-    else MLCT_TH(2, false);
-#undef MLCT_TH
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (pass == 1) return launch_tri_pass<1, true>(s, m, plan, zbits, nullptr, y, hs, hub, part);
-  return off32 ? launch_tri_pass<2, true>(s, m, plan, nullptr, y, nullptr, hs, hub, part)
-               : launch_tri_pass<2, false>(s, m, plan, nullptr, y, nullptr, hs, hub, part);
 }
 
 hipError_t launch_slq_spmm(hipStream_t s, const CsrMat& m, const double* w, double* u,
