@@ -2325,7 +2325,8 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
   CHECK(set_device(ctx));
   // ---- workspace sizes ----
   const size_t nb = blocks.size();
-  size_t bytes = align8(nb * sizeof(BatchBlock)) + 256;
+  size_t bytes = align8(nb * sizeof(BatchBlock)) + align8(nb * sizeof(BatchBlockPost)) +
+                 align8(nitems * sizeof(BatchItemPost)) + 256;
   for (const HostBlock& hb : blocks) {
     const int64_t d = items[hb.item].op->d;
     const CsrStepPlan plan = plan_csr(d, items[hb.item].op->tuned_groups);
@@ -2350,9 +2351,16 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
   void* ws;
   CHECK(ws_get(ctx, WS_BATCH, bytes, &ws));
   Carver cv{static_cast<char*>(ws)};
+  // the tables first, in one piece: one copy brings them over
   BatchBlock* dtab = cv.take<BatchBlock>(nb);
+  BatchBlockPost* dpost = cv.take<BatchBlockPost>(nb);
+  BatchItemPost* ditems = cv.take<BatchItemPost>(nitems);
+  int32_t* dxblk = cv.take<int32_t>(8 * nb);
+  int32_t* dxg0 = cv.take<int32_t>(8 * nb);
+  int64_t* dxbase = cv.take<int64_t>(8 * nb);
+  const size_t table_bytes = cv.off;
   std::vector<BatchBlock> tab(nb);
-  std::vector<double*> dots(nb);
+  std::vector<BatchBlockPost> post(nb);
   for (size_t bi = 0; bi < nb; ++bi) {
     const HostBlock& hb = blocks[bi];
     const mlct_op* op = items[hb.item].op;
@@ -2366,7 +2374,8 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     B.v0 = cv.take<float>((size_t)op->d * 64);
     B.v1 = cv.take<float>((size_t)op->d * 64);
     B.part = cv.take<double>((size_t)(hb.steps + 1) * 2 * plan.ngroups * 64);
-    dots[bi] = cv.take<double>((size_t)(hb.steps + 1) * 2 * 64);
+    post[bi] = BatchBlockPost{B.part, cv.take<double>((size_t)(hb.steps + 1) * 2 * 64), nullptr, 0,
+                              plan.ngroups, hb.steps, hb.active, hb.degree};
     B.src = ProbeSrc{items[hb.item].seed, hb.first_id, nullptr, 0, hb.active};
     const double a = items[hb.item].a, b = items[hb.item].b;
     B.alpha = 2.0 / (b - a);
@@ -2385,9 +2394,6 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     qst[i] = cv.take<double>((size_t)totals[i] + 3 * MLCT_MAX_LEVELS);
   }
   mlct_result* dres = cv.take<mlct_result>(nitems);
-  int32_t* dxblk = cv.take<int32_t>(8 * nb);
-  int32_t* dxg0 = cv.take<int32_t>(8 * nb);
-  int64_t* dxbase = cv.take<int64_t>(8 * nb);
   int64_t* dslots = cv.take<int64_t>(variants.size() * (max_steps + 1) * 8);
   int32_t* dcnt = cv.take<int32_t>(nb + 1);
   int32_t* dabort = cv.take<int32_t>(2);
@@ -2463,18 +2469,39 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     xoff[v][8] = pos - 8 * b0;
   }
   hipStream_t s = ctx->stream;
-  HIPCHK(ctx, hipMemcpyAsync(dtab, tab.data(), nb * sizeof(BatchBlock), hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemcpyAsync(dxblk, xblk.data(), 8 * nb * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemcpyAsync(dxg0, xg0.data(), 8 * nb * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemcpyAsync(dxbase, xbase.data(), 8 * nb * sizeof(int64_t), hipMemcpyHostToDevice, s));
-  // ---- coefficients ----
+  std::vector<BatchItemPost> ipost(nitems);
+  int max_n = 1;
   for (int i = 0; i < nitems; ++i) {
-    const int n = top[i];
-    double* ls = coef[i] + (size_t)(interp ? lvs[i].L : 1) * (n + 1);
-    if (!interp) {
-      HIPCHK(ctx, launch_cheb_dct(s, items[i].f.kind, items[i].f.power, items[i].a, items[i].b, n,
-                                  coef[i], ls));
-    } else {
+    const mlct_batch_item& it = items[i];
+    ipost[i] = BatchItemPost{it.f.kind, top[i],  it.f.power, it.a,
+                             it.b,      coef[i], mu[i],      qst[i],
+                             qst[i] + totals[i], lvs[i]};
+    max_n = std::max(max_n, top[i]);
+  }
+  for (size_t bi = 0; bi < nb; ++bi) {
+    const HostBlock& hb = blocks[bi];
+    post[bi].ldmu = top[hb.item] + 1;
+    post[bi].mu = mu[hb.item] + hb.first_id * post[bi].ldmu;
+  }
+  std::vector<char> tables(table_bytes);
+  auto put = [&](const void* dev, const void* src, size_t n) {
+    std::memcpy(tables.data() + (static_cast<const char*>(dev) - static_cast<const char*>(ws)), src, n);
+  };
+  put(dtab, tab.data(), nb * sizeof(BatchBlock));
+  put(dpost, post.data(), nb * sizeof(BatchBlockPost));
+  put(ditems, ipost.data(), nitems * sizeof(BatchItemPost));
+  put(dxblk, xblk.data(), 8 * nb * sizeof(int32_t));
+  put(dxg0, xg0.data(), 8 * nb * sizeof(int32_t));
+  put(dxbase, xbase.data(), 8 * nb * sizeof(int64_t));
+  HIPCHK(ctx, hipMemcpyAsync(ws, tables.data(), table_bytes, hipMemcpyHostToDevice, s));
+  // ---- coefficients ----
+  if (!interp) {
+    for (int i0 = 0; i0 < nitems; i0 += 65535)
+      HIPCHK(ctx, launch_cheb_dct_batched(s, ditems + i0, std::min(65535, nitems - i0), max_n));
+  } else {
+    for (int i = 0; i < nitems; ++i) {
+      const int n = top[i];
+      double* ls = coef[i] + (size_t)lvs[i].L * (n + 1);
       for (int k = 0; k < lvs[i].L; ++k)
         HIPCHK(ctx, launch_cheb_dct(s, items[i].f.kind, items[i].f.power, items[i].a, items[i].b,
                                     lvs[i].degree[k], coef[i] + (size_t)k * (n + 1), ls));
@@ -2580,20 +2607,12 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     }
   }
   // ---- moments, levels ----
-  for (size_t bi = 0; bi < nb; ++bi) {
-    const HostBlock& hb = blocks[bi];
-    HIPCHK(ctx, launch_reduce_partials(s, tab[bi].part, hb.steps + 1, 2, tab[bi].ngroups, 64,
-                                       dots[bi]));
-    HIPCHK(ctx, launch_assemble_moments(s, dots[bi], hb.steps + 1, 64, hb.active, mode, hb.degree,
-                                        mu[hb.item] + hb.first_id * (top[hb.item] + 1),
-                                        top[hb.item] + 1));
-  }
-  for (int i = 0; i < nitems; ++i) {
-    const int n = top[i];
-    double* ls = coef[i] + (size_t)(interp ? lvs[i].L : 1) * (n + 1);
-    HIPCHK(ctx, launch_level_combine(s, mu[i], n + 1, coef[i], ls, lvs[i], qst[i],
-                                     qst[i] + totals[i], dres + i));
-  }
+  // (grids of 65,535 rows at most in y)
+  for (size_t b0 = 0; b0 < nb; b0 += 65535)
+    HIPCHK(ctx, launch_batch_moments(s, dpost + b0, (int)std::min<size_t>(65535, nb - b0), max_steps,
+                                     mode));
+  for (int i0 = 0; i0 < nitems; i0 += 65535)
+    HIPCHK(ctx, launch_batch_levels(s, ditems + i0, std::min(65535, nitems - i0), dres + i0));
   std::vector<mlct_result> h(nitems);
   HIPCHK(ctx, hipMemcpyAsync(h.data(), dres, nitems * sizeof(mlct_result), hipMemcpyDeviceToHost, s));
   int32_t aborted = 0;

@@ -202,7 +202,8 @@ hipError_t launch_reduce_partials(hipStream_t s, const double* part, int steps, 
 hipError_t launch_assemble_moments(hipStream_t s, const double* dots, int steps, int width,
                                    int active, int mode, int n, double* mu, int64_t ldmu);
 // Per level: Q per probe (into q_dev), mean, unbiased variance and the
-// largest |mu_j|/mu_0; then the multilevel sum into result_dev.
+// largest |mu_j|/mu_0 (by way of ratio_dev, 3 x MLCT_MAX_LEVELS doubles); then
+// the multilevel sum into result_dev.
 struct LevelDesc {
   int32_t degree[MLCT_MAX_LEVELS];
   int64_t m[MLCT_MAX_LEVELS];
@@ -219,8 +220,32 @@ constexpr int kStatsGroups = 1024;
 hipError_t launch_op_stats(hipStream_t s, const mlct_op* op, double* partial, double* out);
 hipError_t launch_level_combine(hipStream_t s, const double* mu, int64_t ldmu,
                                 const double* coef, const double* log_scale,
-                                const LevelDesc& lv, double* q_dev, double* stats_dev,
+                                const LevelDesc& lv, double* q_dev, double* ratio_dev,
                                 mlct_result* result_dev);
+// The same for a batch: one probe block's partials and moment rows, and one
+// item's coefficients and levels (interp: coefficients by launch_cheb_dct).
+struct BatchBlockPost {
+  const double* part;
+  double* dots;
+  double* mu;
+  int64_t ldmu;
+  int ngroups, steps, active, degree;
+};
+struct BatchItemPost {
+  int kind, n;
+  double power, a, b;
+  double* coef;  // [levels or 1][n + 1], then the log-scale
+  const double* mu;
+  double* q;
+  double* ratio;
+  LevelDesc lv;
+};
+hipError_t launch_cheb_dct_batched(hipStream_t s, const BatchItemPost* items, int nitems,
+                                   int max_n);
+hipError_t launch_batch_moments(hipStream_t s, const BatchBlockPost* blocks, int nblocks,
+                                int max_steps, int mode);
+hipError_t launch_batch_levels(hipStream_t s, const BatchItemPost* items, int nitems,
+                               mlct_result* out);
 
 // ---- CSR recurrence (k_csr.hip) -------------------------------------------
 struct CsrStepPlan {

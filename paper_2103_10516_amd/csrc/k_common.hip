@@ -17,10 +17,9 @@ namespace {
 // cos(pi - t) = -cos t), so each workgroup evaluates n/2 + 1 cosines once
 // into LDS; workgroup w computes c_j for j = 256 w .. 256 w + 255, each as
 // one sequential sum over k with the index advanced by additions.
-__global__ __launch_bounds__(256) void cheb_dct_kernel(int kind, double power, double a,
-                                                       double b, int n, double* __restrict__ c,
-                                                       double* __restrict__ log_scale) {
-  extern __shared__ double lds[];
+__device__ __forceinline__ void cheb_dct_wg(int kind, double power, double a, double b, int n,
+                                            double* __restrict__ c,
+                                            double* __restrict__ log_scale, double* lds) {
   double* fk = lds;              // n + 1 samples
   double* cs = lds + (n + 1);    // cos(pi r / n), r = 0 .. n/2
   const double half = 0.5 * (b - a), mid = 0.5 * (a + b);
@@ -36,6 +35,9 @@ __global__ __launch_bounds__(256) void cheb_dct_kernel(int kind, double power, d
   if (j <= n) {
     double s = 0.0;
     int jk = 0;  // j k mod 2n, advanced by j each step (j <= n < 2n)
+    // (unrolled: the LDS reads of eight terms are in flight at once; n = 256
+    // in 34 us one term at a time)
+#pragma unroll 8
     for (int k = 0; k <= n; ++k) {
       const int r = jk > n ? two_n - jk : jk;
       jk += j;
@@ -49,6 +51,22 @@ __global__ __launch_bounds__(256) void cheb_dct_kernel(int kind, double power, d
     c[j] = s;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && log_scale) *log_scale = (kind == MLCT_EXP) ? mid : 0.0;
+}
+
+__global__ __launch_bounds__(256) void cheb_dct_kernel(int kind, double power, double a,
+                                                       double b, int n, double* __restrict__ c,
+                                                       double* __restrict__ log_scale) {
+  extern __shared__ double lds[];
+  cheb_dct_wg(kind, power, a, b, n, c, log_scale, lds);
+}
+
+// The items of a batch (blockIdx.y), each with one interpolant.
+__global__ __launch_bounds__(256) void cheb_dct_batched_kernel(
+    const BatchItemPost* __restrict__ items) {
+  extern __shared__ double lds[];
+  const BatchItemPost& it = items[blockIdx.y];
+  if ((int)blockIdx.x * 256 > it.n) return;
+  cheb_dct_wg(it.kind, it.power, it.a, it.b, it.n, it.coef, it.coef + it.n + 1, lds);
 }
 
 // flags[0]: bit0 rowptr[0] != 0, bit1 decreasing rowptr, bit2 rowptr[d] != nnz,
@@ -81,13 +99,12 @@ __global__ void csr_validate_kernel(const int32_t* __restrict__ rowptr,
 // groups g = w, w + 4, w + 8, ... with four interleaved accumulators, and
 // the partial sums are combined in a fixed order, so the result does not
 // depend on timing.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __restrict__ part,
-                                                              int ngroups, int width,
-                                                              double* __restrict__ dots) {
+__device__ __forceinline__ void reduce_row(const double* __restrict__ part, int64_t row,
+                                           int chunk, int ngroups, int width,
+                                           double* __restrict__ dots) {
   __shared__ double sh[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = blockIdx.x;
-  const int p = blockIdx.y * 64 + lane;
+  const int p = chunk * 64 + lane;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   if (p < width) {
     const double* src = part + row * ngroups * width + p;
@@ -104,40 +121,72 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __re
     dots[row * width + p] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
 }
 
+__global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __restrict__ part,
+                                                              int ngroups, int width,
+                                                              double* __restrict__ dots) {
+  reduce_row(part, blockIdx.x, blockIdx.y, ngroups, width, dots);
+}
+
+// The probe blocks of a batch (blockIdx.y), 64 probes each.
+__global__ __launch_bounds__(256) void reduce_batched_kernel(
+    const BatchBlockPost* __restrict__ blocks) {
+  const BatchBlockPost& b = blocks[blockIdx.y];
+  if ((int)blockIdx.x < 2 * (b.steps + 1))
+    reduce_row(b.part, blockIdx.x, 0, b.ngroups, 64, b.dots);
+}
+
 // Moment table rows from the per-step dot products.
 // Direct form: mu_0 = z.z, mu_j = z.v_j.
 // Symmetric form: mu_1 = v_1.v_0, mu_2 = 2 v_1.v_1 - mu_0,
 // mu_{2s-1} = 2 v_s.v_{s-1} - mu_1 and mu_{2s} = 2 v_s.v_s - mu_0 for s >= 2.
-__global__ void assemble_moments_kernel(const double* __restrict__ dots, int steps, int width,
-                                        int active, int mode, int n, double* __restrict__ mu,
-                                        int64_t ldmu) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= active) return;
-  auto D = [&](int s, int slot) { return dots[((int64_t)s * 2 + slot) * width + p]; };
-  double* row = mu + (int64_t)p * ldmu;
-  const double mu0 = D(0, 0);
-  row[0] = mu0;
-  if (mode == MLCT_DIRECT) {
-    for (int j = 1; j <= n; ++j) row[j] = D(j, 0);
-    return;
+// One thread per (probe, step): each has its own two entries (one thread per
+// probe and all steps took 26 us at degree 256, the stores of a wave each to
+// another row).
+__device__ __forceinline__ void assemble_at(const double* __restrict__ dots, int s, int width,
+                                            int p, int mode, int n, double* __restrict__ row) {
+  auto D = [&](int st, int slot) { return dots[((int64_t)st * 2 + slot) * width + p]; };
+  if (s == 0) {
+    row[0] = D(0, 0);
+  } else if (mode == MLCT_DIRECT) {
+    if (s <= n) row[s] = D(s, 0);
+  } else if (s == 1) {
+    if (n >= 1) row[1] = D(1, 0);
+    if (n >= 2) row[2] = 2.0 * D(1, 1) - D(0, 0);
+  } else {
+    if (2 * s - 1 <= n) row[2 * s - 1] = 2.0 * D(s, 0) - D(1, 0);
+    if (2 * s <= n) row[2 * s] = 2.0 * D(s, 1) - D(0, 0);
   }
-  if (n < 1) return;
-  const double mu1 = D(1, 0);
-  row[1] = mu1;
-  if (n >= 2) row[2] = 2.0 * D(1, 1) - mu0;
-  for (int s = 2; s < steps; ++s) {
-    if (2 * s - 1 <= n) row[2 * s - 1] = 2.0 * D(s, 0) - mu1;
-    if (2 * s <= n) row[2 * s] = 2.0 * D(s, 1) - mu0;
-  }
+}
+
+// blockIdx.x: 64 probes; blockIdx.y: four steps.
+__global__ __launch_bounds__(256) void assemble_moments_kernel(const double* __restrict__ dots,
+                                                               int steps, int width, int active,
+                                                               int mode, int n,
+                                                               double* __restrict__ mu,
+                                                               int64_t ldmu) {
+  const int p = blockIdx.x * 64 + (threadIdx.x & 63);
+  const int s = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (p < active && s < steps) assemble_at(dots, s, width, p, mode, n, mu + (int64_t)p * ldmu);
+}
+
+__global__ __launch_bounds__(256) void assemble_batched_kernel(
+    const BatchBlockPost* __restrict__ blocks, int mode) {
+  const BatchBlockPost& b = blocks[blockIdx.y];
+  const int p = threadIdx.x & 63;
+  const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (p < b.active && s <= b.steps)
+    assemble_at(b.dots, s, 64, p, mode, b.degree, b.mu + (int64_t)p * b.ldmu);
 }
 
 constexpr int kCombThreads = 256;
 
-__device__ double block_sum_fixed(double v, double* sh) {
-  sh[threadIdx.x] = v;
+// Sums and maxima over a team of kCombThreads threads (t: the thread's index
+// in it); every team of the workgroup takes part.
+__device__ double team_sum_fixed(double v, double* sh, int t) {
+  sh[t] = v;
   __syncthreads();
   for (int st = kCombThreads / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
+    if (t < st) sh[t] += sh[t + st];
     __syncthreads();
   }
   const double r = sh[0];
@@ -145,11 +194,11 @@ __device__ double block_sum_fixed(double v, double* sh) {
   return r;
 }
 
-__device__ double block_max(double v, double* sh) {
-  sh[threadIdx.x] = v;
+__device__ double team_max(double v, double* sh, int t) {
+  sh[t] = v;
   __syncthreads();
   for (int st = kCombThreads / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + st]);
+    if (t < st) sh[t] = fmax(sh[t], sh[t + st]);
     __syncthreads();
   }
   const double r = sh[0];
@@ -157,60 +206,101 @@ __device__ double block_max(double v, double* sh) {
   return r;
 }
 
-// One workgroup per level k (eq. def:qlevels):
+// Waves of level k in level_values: one per 64 probes, at most kRatios over all
+// levels (each leaves one ratio).
+constexpr int kRatios = 3 * MLCT_MAX_LEVELS;
+__host__ __device__ inline int level_waves(const LevelDesc& lv, int k) {
+  const int64_t units = (lv.m[k] + 63) / 64, most = kRatios / lv.L;
+  return (int)(units < most ? units : most);
+}
+
+// Level variables (eq. def:qlevels), wave w:
 //   Q^{(p)} = sum_{j = l_{k-1}+1}^{l_k} c_j mu_j^{(p)}   (truncation), or
 //   Q^{(p)} = z^T p_{l_k} z - z^T p_{l_{k-1}} z          (separate interpolants),
-// then the level mean and the unbiased sample variance, and max |mu_j| / mu_0.
-__global__ __launch_bounds__(kCombThreads) void level_stats_kernel(
-    const double* __restrict__ mu, int64_t ldmu, const double* __restrict__ coef, LevelDesc lv,
-    double* __restrict__ q, double* __restrict__ stats) {
-  __shared__ double sh[kCombThreads];
-  const int k = blockIdx.x;
+// and the largest |mu_j| / mu_0 of its probes into ratio[w].  A lane sums its
+// probe's row in degree order; the rows come through LDS in pieces of 32
+// degrees, so that the loads are coalesced (a lane walking its own row took
+// 150 us for 3,712 probes).
+__device__ void level_values(const double* __restrict__ mu, int64_t ldmu,
+                             const double* __restrict__ coef, const LevelDesc& lv, int w,
+                             double* __restrict__ q, double* __restrict__ ratio) {
+  constexpr int kPiece = 32;
+  __shared__ double tile[64][kPiece + 1];
+  const int lane = threadIdx.x;
+  int k = 0, first_w = 0;
+  while (k < lv.L && w - first_w >= level_waves(lv, k)) first_w += level_waves(lv, k++);
+  if (k >= lv.L) return;
   const int hi = lv.degree[k];
   const int lo = k ? lv.degree[k - 1] : -1;
-  const int64_t mk = lv.m[k], o = lv.off[k];
   const double* ch = lv.interp ? coef + (int64_t)k * lv.coef_stride : coef;
   const double* cl = (lv.interp && k) ? coef + (int64_t)(k - 1) * lv.coef_stride : nullptr;
-  double s = 0.0, mr = 0.0;
-  for (int64_t p = threadIdx.x; p < mk; p += kCombThreads) {
-    const double* r = mu + (o + p) * ldmu;
-    double qv = 0.0;
-    if (!lv.interp) {
-      for (int j = max(lo + 1, lv.jmin); j <= hi; ++j) qv += ch[j] * r[j];
-    } else {
-      for (int j = lv.jmin; j <= hi; ++j) qv += ch[j] * r[j];
-      if (cl) {
-        double ql = 0.0;
-        for (int j = lv.jmin; j <= lo; ++j) ql += cl[j] * r[j];
-        qv -= ql;
+  const int j0 = lv.interp ? lv.jmin : max(lo + 1, lv.jmin);
+  const int nw = level_waves(lv, k);
+  double mr = 0.0;
+  for (int64_t u = w - first_w; u * 64 < lv.m[k]; u += nw) {
+    const int64_t first = lv.off[k] + u * 64;
+    const int np = (int)min<int64_t>(64, lv.m[k] - u * 64);
+    double qv = 0.0, ql = 0.0, inv0 = 0.0;
+    for (int b = 0; b <= hi; b += kPiece) {
+      const int c = min(kPiece, hi + 1 - b);
+      for (int e = lane; e < np * kPiece; e += 64) {
+        const int p = e / kPiece, j = e % kPiece;
+        if (j < c) tile[p][j] = mu[(first + p) * ldmu + b + j];
       }
+      __syncthreads();
+      if (lane < np) {
+        if (b == 0) inv0 = 1.0 / tile[lane][0];
+        for (int j = 0; j < c; ++j) {
+          const double r = tile[lane][j];
+          mr = fmax(mr, fabs(r) * inv0);
+          if (b + j >= j0) qv += ch[b + j] * r;
+          if (cl && b + j >= j0 && b + j <= lo) ql += cl[b + j] * r;
+        }
+      }
+      __syncthreads();
     }
-    q[o + p] = qv;
-    s += qv;
-    const double inv0 = 1.0 / r[0];
-    for (int j = 0; j <= hi; ++j) mr = fmax(mr, fabs(r[j]) * inv0);
+    if (lane < np) q[first + lane] = cl ? qv - ql : qv;
   }
-  const double mean = block_sum_fixed(s, sh) / (double)mk;
-  double ss = 0.0;
-  for (int64_t p = threadIdx.x; p < mk; p += kCombThreads) {
-    const double dlt = q[o + p] - mean;
-    ss += dlt * dlt;
-  }
-  ss = block_sum_fixed(ss, sh);
-  mr = block_max(mr, sh);
-  if (threadIdx.x == 0) {
-    stats[3 * k + 0] = mean;
-    stats[3 * k + 1] = mk > 1 ? ss / (double)(mk - 1) : NAN;
-    stats[3 * k + 2] = mr;
-  }
+  for (int o = 32; o > 0; o >>= 1) mr = fmax(mr, __shfl_xor(mr, o, 64));
+  if (lane == 0) ratio[w] = mr;
 }
 
-// Multilevel estimator (eq. eqn:multiEstimator): Gamma = sum_k mean_k and
-// its variance estimate sum_k s_k^2 / m_k, summed over k in order.
-__global__ void level_finalize_kernel(const double* __restrict__ stats, LevelDesc lv,
-                                      const double* __restrict__ coef,
-                                      const double* __restrict__ log_scale,
-                                      mlct_result* __restrict__ out) {
+// Mean and unbiased variance of every level and the largest ratio, four
+// levels at a time (a team of 256 threads each), then the multilevel
+// estimator (eq. eqn:multiEstimator): Gamma = sum_k mean_k and its variance
+// estimate sum_k s_k^2 / m_k, summed over k in order.
+constexpr int kTeams = 4;
+__device__ void level_finish(const LevelDesc& lv, const double* __restrict__ coef,
+                             const double* __restrict__ log_scale, const double* __restrict__ q,
+                             const double* __restrict__ ratio, mlct_result* __restrict__ out) {
+  __shared__ double sh[kTeams][kCombThreads];
+  __shared__ double st[MLCT_MAX_LEVELS][3];
+  const int team = threadIdx.x / kCombThreads, t = threadIdx.x % kCombThreads;
+  for (int k0 = 0; k0 < lv.L; k0 += kTeams) {
+    const int k = k0 + team;
+    const int64_t mk = k < lv.L ? lv.m[k] : 0, o = k < lv.L ? lv.off[k] : 0;
+    double s = 0.0, mr = 0.0;
+    for (int64_t p = t; p < mk; p += kCombThreads) s += q[o + p];
+    if (k < lv.L) {
+      int w = 0;
+      for (int i = 0; i < k; ++i) w += level_waves(lv, i);
+      if (t < level_waves(lv, k)) mr = ratio[w + t];
+    }
+    const double mean = team_sum_fixed(s, sh[team], t) / (double)mk;
+    double ss = 0.0;
+    for (int64_t p = t; p < mk; p += kCombThreads) {
+      const double dlt = q[o + p] - mean;
+      ss += dlt * dlt;
+    }
+    ss = team_sum_fixed(ss, sh[team], t);
+    mr = team_max(mr, sh[team], t);
+    if (t == 0 && k < lv.L) {
+      st[k][0] = mean;
+      st[k][1] = mk > 1 ? ss / (double)(mk - 1) : NAN;
+      st[k][2] = mr;
+    }
+  }
+  __syncthreads();
   if (threadIdx.x != 0) return;
   double v = 0.0, var = 0.0, mr = 0.0;
   uint32_t flags = 0;
@@ -219,12 +309,12 @@ __global__ void level_finalize_kernel(const double* __restrict__ stats, LevelDes
   const double* ctop = lv.interp ? coef + (int64_t)(lv.L - 1) * lv.coef_stride : coef;
   for (int j = 0; j < lv.jmin && j <= n; ++j) v += ctop[j] * lv.low_tr[j];
   for (int k = 0; k < lv.L; ++k) {
-    v += stats[3 * k];
-    if (lv.m[k] > 1) var += stats[3 * k + 1] / (double)lv.m[k];
+    v += st[k][0];
+    if (lv.m[k] > 1) var += st[k][1] / (double)lv.m[k];
     else flags |= MLCT_FLAG_FEW_SAMPLES;
-    mr = fmax(mr, stats[3 * k + 2]);
-    out->level_mean[k] = stats[3 * k];
-    out->level_var[k] = stats[3 * k + 1];
+    mr = fmax(mr, st[k][2]);
+    out->level_mean[k] = st[k][0];
+    out->level_var[k] = st[k][1];
   }
   for (int k = lv.L; k < MLCT_MAX_LEVELS; ++k) {
     out->level_mean[k] = 0.0;
@@ -240,6 +330,40 @@ __global__ void level_finalize_kernel(const double* __restrict__ stats, LevelDes
   out->est_var = var;
   out->max_moment_ratio = mr;
   out->flags = flags;
+}
+
+__global__ __launch_bounds__(64) void level_values_kernel(const double* __restrict__ mu,
+                                                          int64_t ldmu,
+                                                          const double* __restrict__ coef,
+                                                          LevelDesc lv, double* __restrict__ q,
+                                                          double* __restrict__ ratio) {
+  level_values(mu, ldmu, coef, lv, blockIdx.x, q, ratio);
+}
+
+__global__ __launch_bounds__(kTeams* kCombThreads) void level_finish_kernel(
+    LevelDesc lv, const double* __restrict__ coef, const double* __restrict__ log_scale,
+    const double* __restrict__ q, const double* __restrict__ ratio,
+    mlct_result* __restrict__ out) {
+  level_finish(lv, coef, log_scale, q, ratio, out);
+}
+
+__global__ __launch_bounds__(64) void level_values_batched_kernel(
+    const BatchItemPost* __restrict__ items) {
+  const BatchItemPost& it = items[blockIdx.y];
+  level_values(it.mu, it.n + 1, it.coef, it.lv, blockIdx.x, it.q, it.ratio);
+}
+
+__global__ __launch_bounds__(kTeams* kCombThreads) void level_finish_batched_kernel(
+    const BatchItemPost* __restrict__ items, mlct_result* __restrict__ out) {
+  const BatchItemPost& it = items[blockIdx.x];
+  level_finish(it.lv, it.coef, it.coef + (int64_t)(it.lv.interp ? it.lv.L : 1) * (it.n + 1), it.q,
+               it.ratio, out + blockIdx.x);
+}
+
+int level_waves_all(const LevelDesc& lv) {
+  int w = 0;
+  for (int k = 0; k < lv.L; ++k) w += level_waves(lv, k);
+  return w;
 }
 
 }  // namespace
@@ -270,19 +394,45 @@ hipError_t launch_reduce_partials(hipStream_t s, const double* part, int steps, 
 
 hipError_t launch_assemble_moments(hipStream_t s, const double* dots, int steps, int width,
                                    int active, int mode, int n, double* mu, int64_t ldmu) {
-  assemble_moments_kernel<<<(active + 63) / 64, 64, 0, s>>>(dots, steps, width, active, mode,
-                                                             n, mu, ldmu);
+  const dim3 grid((active + 63) / 64, (steps + 3) / 4);
+  assemble_moments_kernel<<<grid, 256, 0, s>>>(dots, steps, width, active, mode, n, mu, ldmu);
   return hipGetLastError();
 }
 
 hipError_t launch_level_combine(hipStream_t s, const double* mu, int64_t ldmu,
                                 const double* coef, const double* log_scale,
-                                const LevelDesc& lv, double* q_dev, double* stats_dev,
+                                const LevelDesc& lv, double* q_dev, double* ratio_dev,
                                 mlct_result* result_dev) {
-  level_stats_kernel<<<lv.L, kCombThreads, 0, s>>>(mu, ldmu, coef, lv, q_dev, stats_dev);
+  level_values_kernel<<<level_waves_all(lv), 64, 0, s>>>(mu, ldmu, coef, lv, q_dev, ratio_dev);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  level_finalize_kernel<<<1, 64, 0, s>>>(stats_dev, lv, coef, log_scale, result_dev);
+  level_finish_kernel<<<1, kTeams * kCombThreads, 0, s>>>(lv, coef, log_scale, q_dev, ratio_dev,
+                                                          result_dev);
+  return hipGetLastError();
+}
+
+hipError_t launch_cheb_dct_batched(hipStream_t s, const BatchItemPost* items, int nitems,
+                                   int max_n) {
+  const size_t lds = (size_t)(max_n + 1 + max_n / 2 + 1) * sizeof(double);
+  cheb_dct_batched_kernel<<<dim3((max_n + 256) / 256, nitems), 256, lds, s>>>(items);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_moments(hipStream_t s, const BatchBlockPost* blocks, int nblocks,
+                                int max_steps, int mode) {
+  reduce_batched_kernel<<<dim3(2 * (max_steps + 1), nblocks), 256, 0, s>>>(blocks);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  assemble_batched_kernel<<<dim3((max_steps + 4) / 4, nblocks), 256, 0, s>>>(blocks, mode);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_levels(hipStream_t s, const BatchItemPost* items, int nitems,
+                               mlct_result* out) {
+  level_values_batched_kernel<<<dim3(kRatios, nitems), 64, 0, s>>>(items);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  level_finish_batched_kernel<<<nitems, kTeams * kCombThreads, 0, s>>>(items, out);
   return hipGetLastError();
 }
 
