@@ -1380,21 +1380,35 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
     CHECK(mlct_bounds(ctx, op, steps, seed + kGamma, 0.01, &a, &b));
   }
   // A CSR operator too small to fill the device with one probe block per
-  // launch (fewer than kSmallGroups workgroups per step) and without rows
-  // longer than kHubLen runs its probe blocks in shared launches (the
-  // batched path, whose results equal this function's bit for bit) when
-  // there are at least kSharedBlocks of them; fewer gain less than the
-  // batched path's set-up costs.  (Only below the batch's solo threshold,
-  // from which the batched path would hand the operator back here.)
-  if (op->kind == OP_CSR && prec == MLCT_FP32 && op->csr.hub_n == 0 &&
-      op->d < ctx->batch_solo_rows &&
+  // launch (fewer than kSmallGroups workgroups per step) runs its probe blocks
+  // in shared launches (the batched path, whose results equal this function's
+  // bit for bit) when there are at least kSharedBlocks of them; fewer gain
+  // less than the batched path's set-up costs.  (Only below the batch's solo
+  // threshold, from which the batched path would hand the operator back here.)
+  // Three blocks suffice up to 8,192 rows (2D Laplacian 64^2: 353 -> 306 us; at
+  // 35,937 rows 1,840 -> 2,015).  Operators with rows longer than kHubLen go
+  // there up to 32,768 rows (graph of 20,000 vertices, four blocks: 1,884 ->
+  // 1,347 us; of 100,000: 3,719 -> 4,505).  These two take the shared launches'
+  // memory only where it is small.
+  if (op->kind == OP_CSR && prec == MLCT_FP32 && op->d < ctx->batch_solo_rows &&
       (mode == MLCT_DIRECT || mode == MLCT_DOUBLING) && levels->L >= 1 &&
-      levels->L <= MLCT_MAX_LEVELS && levels->m &&
+      levels->L <= MLCT_MAX_LEVELS && levels->m && levels->degree &&
       (uint64_t)op->d * 64 * 4 <= 0xFFFFFFFFull &&
       plan_csr(op->d, op->tuned_groups).ngroups < kSmallGroups) {
     int64_t blocks = 0;
-    for (int k = 0; k < levels->L; ++k) blocks += (levels->m[k] + kBlockProbes - 1) / kBlockProbes;
-    if (blocks >= kSharedBlocks) {
+    for (int k = 0; k < levels->L; ++k)
+      blocks += levels->m[k] > 0 ? (levels->m[k] + kBlockProbes - 1) / kBlockProbes : 0;
+    const bool usual = op->csr.hub_n == 0 && blocks >= kSharedBlocks;
+    bool small = blocks >= 3 && op->d <= (op->csr.hub_n == 0 ? 8192 : 32768);
+    if (small && !usual) {
+      const int64_t top = std::max(0, levels->degree[levels->L - 1]);
+      const double each = 512.0 * op->d + 1024.0 * (plan_csr(op->d, op->tuned_groups).ngroups + 1) *
+                                              (double)(top + 1);
+      const double most =
+          ctx->ws_limit ? 0.5 * ((double)ctx->ws_limit - (double)ctx->ws_total) : 1073741824.0;
+      small = blocks * each <= most;
+    }
+    if (usual || small) {
       const mlct_batch_item it{op, f, a, b, *levels, seed};
       return mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, out);
     }
