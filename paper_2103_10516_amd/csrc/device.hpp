@@ -88,6 +88,19 @@ __device__ __forceinline__ int bcast16(int v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x150 + I, 0xf, 0xf, false);
 }
 
+// Lanes 16-31 of a with lanes 0-15 of b, and lanes 48-63 with 32-47; lanes
+// 32-63 of a with lanes 0-31 of b.
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
 // First hub row at or past row r, by a 64-way search over the wave's lanes
 // (two loads deep up to 4,096 rows; a binary search's chain of loads takes
 // longer than a short band).

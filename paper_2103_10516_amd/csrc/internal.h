@@ -513,7 +513,6 @@ constexpr int kLanczosMaxSteps = 128;
 struct LanczosState {
   double alpha[kLanczosMaxSteps];
   double beta[kLanczosMaxSteps];
-  double work[3 * kLanczosMaxSteps];
   int k;        // steps completed
   int stopped;  // breakdown reached
 };

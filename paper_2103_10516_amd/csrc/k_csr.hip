@@ -690,16 +690,6 @@ enum { kOpRec = 0, kOpStore = 1, kOpSlq = 2 };
 
 // The slots' PPL x PPL exchange: element e of slot q goes to slot e, element q
 // (a lane had PPL probes of its slot's row, and has one probe of PPL rows).
-__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
 __device__ __forceinline__ void slot_transpose(WideVec<float>::V& v) {
   uint32_t x[4];
 #pragma unroll

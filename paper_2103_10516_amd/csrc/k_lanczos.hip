@@ -7,7 +7,9 @@
 //   Gram-Schmidt twice: full reorthogonalisation);
 //   alpha_j = h_j + h'_j;  beta_j = |w|;  q_{j+1} = w / beta_j.
 // All scalars stay on the device; a step after a breakdown (beta_j tiny) is
-// a no-op.  The extreme eigenvalues of the tridiagonal T_k are found by
+// a no-op.  A step reads the basis three times: for h, for the first update
+// together with h' (each column's piece is kept in registers between the two),
+// and for the second update with the norm.  The extreme eigenvalues of the tridiagonal T_k are found by
 // Sturm-sequence bisection and the last entries of their eigenvectors by
 // inverse iteration, giving the residual bounds |beta_k s_k|.
 #include <cmath>
@@ -19,18 +21,6 @@ namespace mlct {
 namespace {
 
 constexpr int kT = 256;
-
-__device__ double block_sum256(double v, double* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int st = kT / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
 
 // q_0 = z / |z| with z = Rademacher probe 0 of the seed: |z| = sqrt(d).
 __global__ void lz_start_kernel(double* __restrict__ q0, int64_t d, uint64_t seed,
@@ -67,10 +57,16 @@ __global__ __launch_bounds__(256) void lz_hub_chunk_kernel(const int32_t* __rest
 }
 
 // w = A q (+ shift * qs when qs is given), CSR, FP64 arithmetic on FP32 or
-// implicit-1 values: 16 lanes per row (4 rows per wave), the row's entries
-// strided over its lanes (coalesced index and value loads) and added in a
-// fixed shuffle tree; a row longer than kHubLen adds its chunk sums
+// implicit-1 values: 8 lanes per row and two rows per 8 lanes, so that a wave
+// has up to 64 gathers of 8 entries of q under way (16 lanes on one row left
+// it waiting: 171 us a product on the graph of 10^6 vertices).  A row's
+// entries are strided over its lanes (coalesced index and value loads) and
+// added in a fixed shuffle tree; a row longer than kHubLen adds its chunk sums
 // (lz_hub_chunk_kernel) in chunk order.
+constexpr int kRowLanes = 8;
+constexpr int kRowSets = 2;                          // rows per kRowLanes lanes
+constexpr int kWaveRows = 64 / kRowLanes * kRowSets;  // rows per wave
+constexpr int kGather = 4;                           // entries per lane in flight and row
 __global__ __launch_bounds__(kT) void lz_spmv_kernel(
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
     const float* __restrict__ val, int64_t d, const double* __restrict__ q,
@@ -78,39 +74,78 @@ __global__ __launch_bounds__(kT) void lz_spmv_kernel(
     const int32_t* __restrict__ hub_rows, const int32_t* __restrict__ hub_c0, int hub_n,
     const double* __restrict__ hub_part, const LanczosState* st) {
   if (st->stopped) return;
-  const int lane = threadIdx.x & 63, sub = lane & 15;
+  const int lane = threadIdx.x & 63, sub = lane % kRowLanes;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t i0 = wave * 4; i0 < d; i0 += nw * 4) {  // uniform over the wave
-    const int64_t i = i0 + (lane >> 4);
-    double s = 0.0;
-    bool hub = false;
-    if (i < d) {
-      const int t0 = rowptr[i], t1 = rowptr[i + 1];
-      hub = hub_n > 0 && t1 - t0 > kHubLen;
-      if (!hub)
-        for (int t = t0 + sub; t < t1; t += 16) s += (val ? (double)val[t] : 1.0) * q[col[t]];
-    }
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);  // within the 16 lanes
-    if (sub == 0 && i < d) {
-      if (hub) {
-        int lo = 0, hi = hub_n - 1;  // the row is in the table
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (hub_rows[mid] < i) lo = mid + 1; else hi = mid;
-        }
-        s = 0.0;
-        for (int c = hub_c0[lo]; c < hub_c0[lo + 1]; ++c) s += hub_part[c];
+  for (int64_t i0 = wave * kWaveRows; i0 < d; i0 += nw * kWaveRows) {  // uniform over the wave
+    int64_t i[kRowSets];
+    int t[kRowSets], t1[kRowSets];
+    double s[kRowSets];
+    bool hub[kRowSets];
+#pragma unroll
+    for (int r = 0; r < kRowSets; ++r) {
+      i[r] = i0 + r * (64 / kRowLanes) + lane / kRowLanes;
+      s[r] = 0.0;
+      t[r] = t1[r] = 0;
+      if (i[r] < d) {
+        t[r] = rowptr[i[r]];
+        t1[r] = rowptr[i[r] + 1];
       }
-      if (qs) s += shift * qs[i];
-      w[i] = s;
+      hub[r] = hub_n > 0 && t1[r] - t[r] > kHubLen;
+      t[r] = hub[r] ? t1[r] : t[r] + sub;
+    }
+    while (true) {
+      bool more = false;
+#pragma unroll
+      for (int r = 0; r < kRowSets; ++r) more |= t[r] < t1[r];
+      if (!__any(more)) break;
+      int c[kRowSets][kGather];
+      double v[kRowSets][kGather];
+#pragma unroll
+      for (int r = 0; r < kRowSets; ++r)
+#pragma unroll
+        for (int u = 0; u < kGather; ++u) {
+          const int e = t[r] + u * kRowLanes;
+          const bool in = e < t1[r];
+          c[r][u] = in ? col[e] : -1;
+          v[r][u] = in && val ? (double)val[e] : 1.0;
+        }
+#pragma unroll
+      for (int r = 0; r < kRowSets; ++r) {
+        double x[kGather];
+#pragma unroll
+        for (int u = 0; u < kGather; ++u) x[u] = c[r][u] >= 0 ? q[c[r][u]] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kGather; ++u)
+          if (c[r][u] >= 0) s[r] += v[r][u] * x[u];
+        t[r] += kGather * kRowLanes;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kRowSets; ++r) {
+      for (int o = kRowLanes / 2; o > 0; o >>= 1) s[r] += __shfl_xor(s[r], o, 64);
+      if (sub == 0 && i[r] < d) {
+        if (hub[r]) {
+          int lo = 0, hi = hub_n - 1;  // the row is in the table
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (hub_rows[mid] < i[r]) lo = mid + 1; else hi = mid;
+          }
+          s[r] = 0.0;
+          for (int ch = hub_c0[lo]; ch < hub_c0[lo + 1]; ++ch) s[r] += hub_part[ch];
+        }
+        if (qs) s[r] += shift * qs[i[r]];
+        w[i[r]] = s[r];
+      }
     }
   }
 }
 
 // w = M q (+ shift * qs) for one CSR matrix M, long rows through the chunks.
-void lz_csr_product(hipStream_t s, const CsrMat& m, int grid, const double* q, double* w,
-                    double shift, const double* qs, double* hub_part, const LanczosState* st) {
+void lz_csr_product(hipStream_t s, const CsrMat& m, const double* q, double* w, double shift, 
+                    const double* qs, double* hub_part, const LanczosState* st) {
+  const int64_t rows = kT / 64 * kWaveRows;
+  const int grid = (int)((m.nrows + rows - 1) / rows < 4096 ? (m.nrows + rows - 1) / rows : 4096);
   if (m.hub_n > 0)
     lz_hub_chunk_kernel<<<(m.hub_chunks + 3) / 4, 256, 0, s>>>(m.col, m.val, m.hub_cs, m.hub_ce,
                                                                m.hub_chunks, q, hub_part, st);
@@ -132,23 +167,6 @@ __global__ void lz_gemv_kernel(const double* __restrict__ A, int64_t lda, int64_
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) w[i] = s;
   }
-}
-
-// part[c][b] = sum over block b's slice of Q[c] . w, for c = 0..ncols-1.
-__global__ __launch_bounds__(kT) void lz_dots_kernel(const double* __restrict__ Q, int64_t d,
-                                                     const double* __restrict__ w, int ncols,
-                                                     double* __restrict__ part,
-                                                     const LanczosState* st) {
-  __shared__ double sh[kT];
-  if (st->stopped) return;
-  const int c = blockIdx.y;
-  if (c >= ncols) return;
-  const double* qc = Q + (int64_t)c * d;
-  double s = 0.0;
-  for (int64_t n = (int64_t)blockIdx.x * kT + threadIdx.x; n < d; n += (int64_t)gridDim.x * kT)
-    s += qc[n] * w[n];
-  s = block_sum256(s, sh);
-  if (threadIdx.x == 0) part[(int64_t)c * gridDim.x + blockIdx.x] = s;
 }
 
 // Sum of part[0 .. nb) by one wave in a fixed order: lane l adds entries
@@ -177,35 +195,157 @@ __global__ __launch_bounds__(64) void lz_dots_reduce_kernel(const double* __rest
   }
 }
 
-// w -= sum_c h[c] Q[c]
-__global__ void lz_update_kernel(const double* __restrict__ Q, int64_t d, int ncols,
-                                 const double* __restrict__ h, double* __restrict__ w,
-                                 const LanczosState* st) {
-  if (st->stopped) return;
-  for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < d;
-       n += (int64_t)gridDim.x * blockDim.x) {
-    double s = w[n];
-    for (int c = 0; c < ncols; ++c) s -= h[c] * Q[(int64_t)c * d + n];
-    w[n] = s;
+// Lanes swap the halves of 2 M values across lane bit BIT, then of M across the
+// next, ...; once one value is left, plain sums over the remaining bits.
+template <int M, int BIT, int C>
+__device__ __forceinline__ void fold_lanes(double (&v)[C]) {
+  if constexpr (BIT >= 1) {
+    if constexpr (M >= 1) {
+      const bool up = threadIdx.x & BIT;
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const double keep = up ? v[i + M] : v[i], give = up ? v[i] : v[i + M];
+        v[i] = keep + __shfl_xor(give, BIT, 64);
+      }
+    } else {
+      v[0] += __shfl_xor(v[0], BIT, 64);
+    }
+    fold_lanes<M / 2, BIT / 2>(v);
   }
 }
 
-// beta_j = |w| from the partials of w.w; q_{j+1} = w / beta_j, or stop.
-__global__ __launch_bounds__(64) void lz_norm_reduce_kernel(const double* __restrict__ part,
-                                                            int nb, int j, LanczosState* st) {
-  if (st->stopped) return;
-  const double s = wave_sum_fixed(part, nb);
-  if (threadIdx.x != 0) return;
-  const double beta = sqrt(s);
-  st->beta[j] = beta;
-  st->k = j + 1;
-  if (!(beta > 1e-12 * fmax(1.0, fabs(st->alpha[j])))) st->stopped = 1;
+// Sums over the wave's lanes of C values per lane (C = 16, 32 or 64, in place),
+// fixed tree: the sum of value c ends in the lanes l with l / (64 / C) = c.
+// The lanes swap halves of their values, so that C - 1 additions do what C
+// trees of 6 would; the two widest exchanges are register swaps.
+template <int C>
+__device__ __forceinline__ double wave_sums(double (&v)[C]) {
+  auto swap_add = [&](double a, double b, auto&& swap) {
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    swap(x.x, y.x);
+    swap(x.y, y.y);
+    return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+  };
+#pragma unroll
+  for (int i = 0; i < C / 2; ++i) v[i] = swap_add(v[i], v[i + C / 2], swap32);
+#pragma unroll
+  for (int i = 0; i < C / 4; ++i) v[i] = swap_add(v[i], v[i + C / 4], swap16);
+  fold_lanes<C / 8, 8>(v);
+  return v[0];
 }
 
-__global__ void lz_next_kernel(const double* __restrict__ w, int64_t d, int j,
-                               double* __restrict__ qn, const LanczosState* st) {
+// One pass over the basis, a wave per 64 rows at a time (lane = row), with the
+// rows of up to C columns in registers: 64 loads under way per lane.
+//   kDots:   part[c][b] = block b's sums of Q[c] . w
+//   kUpdate: w -= sum_c h[c] Q[c], then the same sums of the new w
+//   kNorm:   w -= sum_c h[c] Q[c], then part[b] = block b's sum of w^2
+// More than 64 columns go through in pieces of 64; for kUpdate all but the last
+// are then read twice.
+enum { kDots = 0, kUpdate = 1, kNorm = 2 };
+template <int MODE, int C>
+__global__ __launch_bounds__(kT) void lz_pass_kernel(const double* __restrict__ Q, int64_t d,
+                                                     int ncols, const double* __restrict__ h,
+                                                     double* __restrict__ w,
+                                                     double* __restrict__ part,
+                                                     const LanczosState* st) {
+  constexpr int kWv = kT / 64, kPieces = (kLanczosMaxSteps + 63) / 64;
+  constexpr int kSpread = 64 / C;  // lanes that hold one column's sum
+  __shared__ double sh[kWv][64];
   if (st->stopped) return;
-  const double inv = 1.0 / st->beta[j];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pieces = (ncols + C - 1) / C;
+  double acc[C == 64 ? kPieces : 1] = {};
+  double nrm = 0.0;
+  const int64_t nw = (int64_t)gridDim.x * kWv;
+  for (int64_t t = (int64_t)blockIdx.x * kWv + wave; t * 64 < d; t += nw) {
+    const int64_t n = t * 64 + lane, nn = n < d ? n : d - 1;
+    double s = n < d ? w[n] : 0.0;
+    double q[C];
+    auto load = [&](int p) {
+#pragma unroll
+      for (int c0 = 0; c0 < C; c0 += 8) {
+        if (p * C + c0 < ncols) {  // uniform
+#pragma unroll
+          for (int c = c0; c < c0 + 8; ++c)
+            q[c] = Q[(int64_t)min(p * C + c, ncols - 1) * d + nn];
+        } else {
+#pragma unroll
+          for (int c = c0; c < c0 + 8; ++c) q[c] = 0.0;
+        }
+      }
+    };
+    if constexpr (MODE != kDots) {
+      for (int p = 0; p < pieces; ++p) {
+        load(p);
+#pragma unroll
+        for (int c0 = 0; c0 < C; c0 += 8) {
+          if (p * C + c0 < ncols) {
+#pragma unroll
+            for (int c = c0; c < c0 + 8; ++c)
+              if (p * C + c < ncols) s -= h[p * C + c] * q[c];
+          }
+        }
+      }
+      if (n < d) w[n] = s;
+      else s = 0.0;
+    }
+    if constexpr (MODE == kNorm) {
+      nrm += s * s;
+    } else {
+#pragma unroll
+      for (int p = C == 64 ? kPieces - 1 : 0; p >= 0; --p) {
+        if (p >= pieces) continue;
+        if (MODE == kDots || p != pieces - 1) load(p);
+#pragma unroll
+        for (int c = 0; c < C; ++c) q[c] *= s;
+        acc[p] += wave_sums<C>(q);
+      }
+    }
+  }
+  if constexpr (MODE == kNorm) {
+    for (int o = 32; o > 0; o >>= 1) nrm += __shfl_xor(nrm, o, 64);
+    if (lane == 0) sh[wave][0] = nrm;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = (sh[0][0] + sh[1][0]) + (sh[2][0] + sh[3][0]);
+  } else {
+#pragma unroll
+    for (int p = 0; p < (C == 64 ? kPieces : 1); ++p) {
+      if (p >= pieces) break;
+      __syncthreads();
+      sh[wave][lane] = acc[p];
+      __syncthreads();
+      const int c = p * C + (int)threadIdx.x;
+      if ((int)threadIdx.x < C && c < ncols) {
+        const int l = threadIdx.x * kSpread;
+        part[(int64_t)c * gridDim.x + blockIdx.x] = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
+      }
+    }
+  }
+}
+
+template <int MODE>
+void lz_pass(hipStream_t s, int grid, const double* Q, int64_t d, int ncols, const double* h,
+             double* w, double* part, const LanczosState* st) {
+  if (ncols <= 16) lz_pass_kernel<MODE, 16><<<grid, kT, 0, s>>>(Q, d, ncols, h, w, part, st);
+  else if (ncols <= 32) lz_pass_kernel<MODE, 32><<<grid, kT, 0, s>>>(Q, d, ncols, h, w, part, st);
+  else lz_pass_kernel<MODE, 64><<<grid, kT, 0, s>>>(Q, d, ncols, h, w, part, st);
+}
+
+// beta_j = |w| from the partials of w.w (every wave adds them, in the same
+// order); q_{j+1} = w / beta_j, or stop.
+__global__ __launch_bounds__(kT) void lz_next_kernel(const double* __restrict__ w, int64_t d,
+                                                     const double* __restrict__ part, int nb, int j,
+                                                     double* __restrict__ qn, LanczosState* st) {
+  if (st->stopped) return;
+  const double beta = sqrt(wave_sum_fixed(part, nb));
+  const bool stop = !(beta > 1e-12 * fmax(1.0, fabs(st->alpha[j])));
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->beta[j] = beta;
+    st->k = j + 1;
+    if (stop) st->stopped = 1;
+  }
+  if (stop) return;
+  const double inv = 1.0 / beta;
   for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < d;
        n += (int64_t)gridDim.x * blockDim.x)
     qn[n] = w[n] * inv;
@@ -223,7 +363,11 @@ __device__ int sturm_count(const double* al, const double* be, int k, double x) 
   return cnt;
 }
 
-__device__ double bisect(const double* al, const double* be, int k, int index) {
+// Eigenvalue number index of T by one wave: each round tries 64 points of the
+// interval, so ten rounds do what 60 bisections would, until the ends are
+// neighbouring numbers.
+__device__ double wave_bisect(const double* al, const double* be, int k, int index) {
+  const int lane = threadIdx.x & 63;
   double lo = 1e300, hi = -1e300;
   for (int i = 0; i < k; ++i) {
     const double r = (i ? fabs(be[i - 1]) : 0.0) + (i + 1 < k ? fabs(be[i]) : 0.0);
@@ -233,10 +377,15 @@ __device__ double bisect(const double* al, const double* be, int k, int index) {
   for (int it = 0; it < 200; ++it) {
     const double mid = 0.5 * (lo + hi);
     if (mid <= lo || mid >= hi) break;
-    if (sturm_count(al, be, k, mid) > index)
-      hi = mid;
-    else
-      lo = mid;
+    const double x = lo + (hi - lo) * ((lane + 1) * (1.0 / 65.0));
+    // the first point with more than index eigenvalues below it
+    const uint64_t above = __ballot(sturm_count(al, be, k, x) > index);
+    const int f = above ? __builtin_ctzll(above) : 64;
+    const double nlo = f > 0 ? __shfl(x, f - 1, 64) : lo;
+    const double nhi = f < 64 ? __shfl(x, f, 64) : hi;
+    if (nlo == lo && nhi == hi) break;
+    lo = nlo;
+    hi = nhi;
   }
   return 0.5 * (lo + hi);
 }
@@ -265,24 +414,36 @@ __device__ double last_component(const double* al, const double* be, int k, doub
   return fabs(x[k - 1]);
 }
 
-__global__ void lz_interval_kernel(LanczosState* st, double margin, double* out) {
-  if (threadIdx.x != 0) return;
+// Two waves: the smallest and the largest Ritz value with their residual
+// bounds, T and the solver's scratch in LDS (one thread over global memory took
+// 910 us for 64 steps).
+__global__ __launch_bounds__(128) void lz_interval_kernel(const LanczosState* st, double margin,
+                                                          double* out) {
+  __shared__ double al[kLanczosMaxSteps], be[kLanczosMaxSteps];
+  __shared__ double work[2][3][kLanczosMaxSteps];
+  __shared__ double th[2], res[2];
   const int k = st->k;
-  double* x = st->work;
-  double* cp = st->work + kLanczosMaxSteps;
-  double* dp = st->work + 2 * kLanczosMaxSteps;
-  const double tmin = bisect(st->alpha, st->beta, k, 0);
-  const double tmax = bisect(st->alpha, st->beta, k, k - 1);
-  const double bk = st->beta[k - 1];
-  const double rmin = fabs(bk) * last_component(st->alpha, st->beta, k, tmin, x, cp, dp);
-  const double rmax = fabs(bk) * last_component(st->alpha, st->beta, k, tmax, x, cp, dp);
-  const double w = tmax - tmin;
-  out[0] = tmin - rmin - margin * w;
-  out[1] = tmax + rmax + margin * w;
-  out[2] = tmin;
-  out[3] = tmax;
-  out[4] = rmin;
-  out[5] = rmax;
+  for (int i = threadIdx.x; i < k; i += 128) {
+    al[i] = st->alpha[i];
+    be[i] = st->beta[i];
+  }
+  __syncthreads();
+  const int e = threadIdx.x >> 6;  // 0: smallest, 1: largest
+  const double theta = wave_bisect(al, be, k, e ? k - 1 : 0);
+  if ((threadIdx.x & 63) == 0) {
+    th[e] = theta;
+    res[e] = fabs(be[k - 1]) *
+             last_component(al, be, k, theta, work[e][0], work[e][1], work[e][2]);
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const double w = th[1] - th[0];
+  out[0] = th[0] - res[0] - margin * w;
+  out[1] = th[1] + res[1] + margin * w;
+  out[2] = th[0];
+  out[3] = th[1];
+  out[4] = res[0];
+  out[5] = res[1];
   out[6] = (double)k;
 }
 
@@ -293,28 +454,27 @@ hipError_t launch_lanczos(hipStream_t s, const mlct_op* op, const void* a64, int
                           double* h, double* part, LanczosState* st, double* out, double* tmp,
                           double* hub_part) {
   const int64_t d = op->d;
-  const int nb = (int)((d + kT - 1) / kT < 1024 ? (d + kT - 1) / kT : 1024);
-  const int grid = nb;
+  // blocks of the passes over the basis: three waves per SIMD
+  const int nb = (int)((d + kT - 1) / kT < 768 ? (d + kT - 1) / kT : 768);
+  const int grid = (int)((d + kT - 1) / kT < 1024 ? (d + kT - 1) / kT : 1024);
   lz_start_kernel<<<grid, kT, 0, s>>>(Q, d, seed, st);
   for (int j = 0; j < steps; ++j) {
     const double* qj = Q + (int64_t)j * d;
     if (op->kind == OP_CSR) {
-      lz_csr_product(s, op->csr, grid, qj, w, 0.0, nullptr, hub_part, st);
+      lz_csr_product(s, op->csr, qj, w, 0.0, nullptr, hub_part, st);
     } else if (op->kind == OP_GRAM_CSR) {  // w = X^T (X q) + lambda q
-      lz_csr_product(s, op->csrx, grid, qj, tmp, 0.0, nullptr, hub_part, st);
-      lz_csr_product(s, op->csr, grid, tmp, w, op->gram_lambda, qj, hub_part, st);
+      lz_csr_product(s, op->csrx, qj, tmp, 0.0, nullptr, hub_part, st);
+      lz_csr_product(s, op->csr, tmp, w, op->gram_lambda, qj, hub_part, st);
     } else
       lz_gemv_kernel<<<grid, kT, 0, s>>>(static_cast<const double*>(a64), lda, d, qj, w, st);
-    for (int pass = 0; pass < 2; ++pass) {
-      lz_dots_kernel<<<dim3(nb, j + 1), kT, 0, s>>>(Q, d, w, j + 1, part, st);
-      lz_dots_reduce_kernel<<<j + 1, 64, 0, s>>>(part, nb, j + 1, h, pass, j, st);
-      lz_update_kernel<<<grid, kT, 0, s>>>(Q, d, j + 1, h, w, st);
-    }
-    lz_dots_kernel<<<dim3(nb, 1), kT, 0, s>>>(w, d, w, 1, part, st);
-    lz_norm_reduce_kernel<<<1, 64, 0, s>>>(part, nb, j, st);
-    lz_next_kernel<<<grid, kT, 0, s>>>(w, d, j, Q + (int64_t)(j + 1) * d, st);
+    lz_pass<kDots>(s, nb, Q, d, j + 1, h, w, part, st);
+    lz_dots_reduce_kernel<<<j + 1, 64, 0, s>>>(part, nb, j + 1, h, 0, j, st);
+    lz_pass<kUpdate>(s, nb, Q, d, j + 1, h, w, part, st);
+    lz_dots_reduce_kernel<<<j + 1, 64, 0, s>>>(part, nb, j + 1, h, 1, j, st);
+    lz_pass<kNorm>(s, nb, Q, d, j + 1, h, w, part, st);
+    lz_next_kernel<<<grid, kT, 0, s>>>(w, d, part, nb, j, Q + (int64_t)(j + 1) * d, st);
   }
-  lz_interval_kernel<<<1, 64, 0, s>>>(st, margin, out);
+  lz_interval_kernel<<<1, 128, 0, s>>>(st, margin, out);
   return hipGetLastError();
 }
 
