@@ -478,10 +478,11 @@ mlct_status mlct_estimate_auto(mlct_ctx* ctx, const mlct_op* op, mlct_func f, do
  * operator on the device and keeps the fastest in the operator (CSR: the cap
  * on workgroups per step, 512 / 1024 / 2048 / 4096, FP32, 64 probes;
  * dense: 32 x 32, 64 x 64 or 128 x 128 square tiles or the skinny split-K
- * kernel (64 or 32 probes x 16 rows per workgroup) in arithmetic ``prec`` at
- * block width B_max; kept as 0, 2, 1 or 3).  Without tuning, blocks of at
- * most 64 probes take the skinny kernel and wider ones the largest square
- * tile that still fills the device.  With a cache file given to mlct_create the decision is written
+ * kernel (16 to 64 probes x 16 to 64 rows per workgroup) in arithmetic
+ * ``prec`` at block width B_max; kept as 0, 2, 1 or 3).  Without tuning, FP64
+ * blocks and FP32 blocks of a dense matrix take the skinny kernel; BF16X3
+ * blocks up to 512 probes and FP32 blocks of a Gram operator up to 64 do, and
+ * wider ones the largest square tile that still fills the device.  With a cache file given to mlct_create the decision is written
  * there, keyed by the operator's shape (dense: and by precision and block
  * width); CSR operators of the same shape pick it up when they are created,
  * dense operators whenever a block of that precision and width runs.

@@ -71,6 +71,17 @@ mlct_status fail(mlct_ctx* ctx, mlct_status st, const char* fmt, ...) {
     if (st_ != MLCT_OK) return st_;    \
   } while (0)
 
+// Frees a workspace slot (the next ws_get allocates it again).
+mlct_status ws_drop(mlct_ctx* ctx, int slot) {
+  DevBuf& b = ctx->slots[slot];
+  if (!b.ptr) return MLCT_OK;
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  HIPCHK(ctx, hipFree(b.ptr));
+  ctx->ws_total -= b.bytes;
+  b = DevBuf{};
+  return MLCT_OK;
+}
+
 // Grow-only workspace slot.  Growing frees the old buffer (hipFree waits for
 // the device), so pointers from an earlier ws_get of the same slot become
 // invalid; callers take all slots they need before enqueuing work.
@@ -81,6 +92,9 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
     *out = b.ptr;
     return MLCT_OK;
   }
+  // packed dense operands are a spare: they give way to what a call needs
+  if (slot != WS_DPACK && ctx->ws_limit && ctx->ws_total - b.bytes + bytes > ctx->ws_limit)
+    CHECK(ws_drop(ctx, WS_DPACK));
   const uint64_t new_total = ctx->ws_total - b.bytes + bytes;
   if (ctx->ws_limit && new_total > ctx->ws_limit)
     return fail(ctx, MLCT_ENOMEM, "workspace of %llu bytes exceeds the limit of %llu",
@@ -104,7 +118,9 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
   void* p = nullptr;
   if (hipMalloc(&p, want) != hipSuccess) {
     (void)hipGetLastError();
-    if (want == bytes || hipMalloc(&p, bytes) != hipSuccess) {
+    const bool spare = slot != WS_DPACK && ctx->slots[WS_DPACK].ptr;
+    if (spare) CHECK(ws_drop(ctx, WS_DPACK));
+    if ((want == bytes && !spare) || hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return fail(ctx, MLCT_ENOMEM, "hipMalloc(%zu) failed", bytes);
     }
@@ -114,17 +130,6 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
   b.bytes = want;
   ctx->ws_total += want;
   *out = p;
-  return MLCT_OK;
-}
-
-// Frees a workspace slot (the next ws_get allocates it again).
-mlct_status ws_drop(mlct_ctx* ctx, int slot) {
-  DevBuf& b = ctx->slots[slot];
-  if (!b.ptr) return MLCT_OK;
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  HIPCHK(ctx, hipFree(b.ptr));
-  ctx->ws_total -= b.bytes;
-  b = DevBuf{};
   return MLCT_OK;
 }
 
@@ -763,7 +768,7 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
                            const void** phi, const void** plo) {
   mlct_op* op = const_cast<mlct_op*>(cop);
   if (!op->pack_hi) {
-    const size_t bytes = dense_pack_bytes(op->d, op->d);
+    const size_t bytes = dense_pack_bytes(MLCT_BF16X3, op->d, op->d);
     void *h = nullptr, *l = nullptr;
     if (hipMalloc(&h, bytes) != hipSuccess || hipMalloc(&l, bytes) != hipSuccess) {
       (void)hipGetLastError();
@@ -776,6 +781,47 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
   }
   *phi = op->pack_hi;
   *plo = op->pack_lo;
+  return MLCT_OK;
+}
+
+// The tile of a block of bpad probes with S steps, and whether it reads packed
+// operands, whose workspace (WS_DPACK) is taken here.  FP32 and FP64 pack
+// matrix and probes anew for each block, which a few steps have to pay for
+// (d = 4096, 64 probes in FP32: 30 us once against 18 us a step).  Where there
+// is no memory for packed operands, the block goes without.
+//
+// BF16X3 and the FP32 blocks of a Gram operator keep the order of their sums:
+// another order makes neither of them more exact, since the split's and the
+// Gram matrix's own rounding stay (FP64 and the FP32 blocks of a given matrix
+// come out as near or nearer: d = 2048, degree 48, 700 probes 2.1e-6 -> 0.8e-6),
+// but it moves BF16X3 moments of a small operator by as much as the split's
+// error (d = 100, 40 probes: 4e-5), and the variances of nuclear norms by 1e-6.
+constexpr int kPackMinSteps = 4;
+constexpr size_t kMaxPack = (size_t)8 << 30;
+mlct_status dense_shape(mlct_ctx* ctx, const mlct_op* op, int prec, int64_t lda, int64_t bpad,
+                        int S, DenseTile* t, bool* packed) {
+  const int choice = dense_choice(ctx, op, prec, bpad);
+  const size_t pa = dense_pack_bytes(prec, op->d, op->d), pv = dense_pack_bytes(prec, bpad, op->d);
+  const bool same_sums = prec == MLCT_BF16X3 || (prec == MLCT_FP32 && op->kind == OP_GRAM);
+  *packed = prec == MLCT_BF16X3 || (S >= kPackMinSteps && pa + 2 * pv <= kMaxPack);
+  if (*packed) {
+    *t = dense_tile(prec, op->d, lda, bpad, true, same_sums, choice);
+    *packed = t->skinny || (prec == MLCT_BF16X3 && t->bm == 128);
+    if (!*packed) return MLCT_OK;
+    mlct_status st = MLCT_OK;
+    const void *a0, *a1;
+    int64_t ld;
+    if (prec == MLCT_BF16X3) {
+      CHECK(dense_operand(ctx, op, prec, &a0, &a1, &ld));
+      st = dense_packed_a(ctx, op, a0, a1, &a0, &a1);
+    }
+    void* w;
+    if (st == MLCT_OK) st = ws_get(ctx, WS_DPACK, prec == MLCT_BF16X3 ? 4 * pv : pa + 2 * pv, &w);
+    if (st != MLCT_ENOMEM) return st;
+    ctx->err.clear();
+    *packed = false;
+  }
+  *t = dense_tile(prec, op->d, lda, bpad, false, same_sums, choice);
   return MLCT_OK;
 }
 
@@ -813,10 +859,9 @@ mlct_status reserve_block_ws(mlct_ctx* ctx, const mlct_op* op, int prec, int mod
   CHECK(ws_get(ctx, WS_V1, (size_t)bpad * op->d * tsz, &tmp));
   CHECK(ws_get(ctx, WS_PART, (size_t)2 * ntiles * bpad * (S + 1) * sizeof(double), &tmp));
   CHECK(ws_get(ctx, WS_MISC, (size_t)(S + 1) * 2 * bpad * sizeof(double), &tmp));
-  const DenseTile tb = dense_tile(prec, op->d, op->d, bpad, dense_choice(ctx, op, prec, bpad));
-  if (prec == MLCT_BF16X3 && (tb.skinny || tb.bm == 128))
-    CHECK(ws_get(ctx, WS_DPACK, 4 * dense_pack_bytes(bpad, op->d), &tmp));
-  return MLCT_OK;
+  DenseTile t;
+  bool packed;
+  return dense_shape(ctx, op, prec, op->d, bpad, S, &t, &packed);
 }
 
 mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, double beta,
@@ -827,10 +872,11 @@ mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, doub
   const void *a0, *a1;
   int64_t lda;
   CHECK(dense_operand(ctx, op, prec, &a0, &a1, &lda));
-  const int tile_choice = dense_choice(ctx, op, prec, bpad);
-  const DenseTile t = dense_tile(prec, d, lda, bpad, tile_choice);
-  const int64_t ntiles = (d + t.bn - 1) / t.bn;
   CHECK(reserve_block_ws(ctx, op, prec, mode, degree, src.active));
+  DenseTile t;
+  bool packed;
+  CHECK(dense_shape(ctx, op, prec, lda, bpad, S, &t, &packed));
+  const int64_t ntiles = (d + t.bn - 1) / t.bn;
   const size_t tsz = prec == MLCT_FP64 ? 8 : 4;
   void *v0, *v1, *part, *dots;
   CHECK(ws_get(ctx, WS_V0, (size_t)bpad * d * tsz, &v0));
@@ -843,22 +889,29 @@ mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, doub
   const size_t pstep = (size_t)2 * ntiles * bpad;
   hipStream_t s = ctx->stream;
   HIPCHK(ctx, launch_dense_probe_init(s, prec, buf[0], d, bpad, src, D));
-  // BF16X3 skinny and 128-wide blocks read A and V_k packed; two packed V
-  // blocks alternate
-  // (V_0 packed here, V_new packed by each step's epilogue; their padding
-  // stays zero)
-  const bool packed = prec == MLCT_BF16X3 && (t.skinny || t.bm == 128);
+  // skinny blocks, and BF16X3's 128-wide ones, read A and V_k packed; two
+  // packed V blocks alternate (V_0 packed here, V_new packed by each step's
+  // epilogue; their padding stays zero)
   const void *pa_hi = nullptr, *pa_lo = nullptr;
   char* vpk[4] = {nullptr, nullptr, nullptr, nullptr};  // (hi, lo) of blocks 0 and 1
   if (packed) {
-    CHECK(dense_packed_a(ctx, op, a0, a1, &pa_hi, &pa_lo));
-    const size_t pb = dense_pack_bytes(bpad, d);
+    const size_t pb = dense_pack_bytes(prec, bpad, d);
     void* w;
-    CHECK(ws_get(ctx, WS_DPACK, 4 * pb, &w));
-    for (int i = 0; i < 4; ++i) vpk[i] = static_cast<char*>(w) + i * pb;
-    HIPCHK(ctx, launch_dense_pack_v(s, static_cast<const float*>(buf[0]), bpad, d, vpk[0],
-                                    vpk[1]));
-    HIPCHK(ctx, hipMemsetAsync(vpk[2], 0, 2 * pb, s));
+    if (prec == MLCT_BF16X3) {
+      CHECK(ws_get(ctx, WS_DPACK, 4 * pb, &w));
+      for (int i = 0; i < 4; ++i) vpk[i] = static_cast<char*>(w) + i * pb;
+      CHECK(dense_packed_a(ctx, op, a0, a1, &pa_hi, &pa_lo));
+      HIPCHK(ctx, launch_dense_pack_v(s, static_cast<const float*>(buf[0]), bpad, d, vpk[0],
+                                      vpk[1]));
+      HIPCHK(ctx, hipMemsetAsync(vpk[2], 0, 2 * pb, s));
+    } else {
+      const size_t pa = dense_pack_bytes(prec, d, d);
+      CHECK(ws_get(ctx, WS_DPACK, pa + 2 * pb, &w));
+      vpk[0] = static_cast<char*>(w) + pa;
+      vpk[2] = vpk[0] + pb;
+      HIPCHK(ctx, launch_dense_pack_plain(s, prec, a0, lda, buf[0], bpad, d, w, vpk[0], vpk[2]));
+      pa_hi = w;
+    }
   }
   const int zdirect = src.entries ? 2 : 1;
   for (int k = 1; k <= S; ++k) {
@@ -877,7 +930,7 @@ mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, doub
     a.zmode = (mode == MLCT_DOUBLING || first) ? 0 : zdirect;
     a.src = src;
     a.part = P + pstep * (k - 1);
-    a.tile_force = tile_choice;
+    a.tile = t;
     if (packed) {
       const int in = (k - 1) & 1, out = k & 1;
       a.pk_a_hi = pa_hi;

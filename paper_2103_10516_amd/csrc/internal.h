@@ -461,6 +461,10 @@ hipError_t launch_tri_cv(hipStream_t s, const long long* w, int64_t m, int64_t n
 // ---- dense recurrence on MFMA (k_dense.hip) --------------------------------
 // Probe blocks of the dense path are probe-major (V^T, bpad x d).
 constexpr int64_t kDenseMaxBlock = 4096;
+struct DenseTile {
+  bool skinny;  // split-K kernel
+  int bm, bn;   // probes x matrix rows per workgroup
+};
 struct DenseStepArgs {
   const void* A0;  // matrix (FP64 / FP32) or its bf16 hi part
   const void* A1;  // bf16 lo part (BF16X3 only)
@@ -472,9 +476,10 @@ struct DenseStepArgs {
   int zmode;
   ProbeSrc src;
   double* part;  // [2][ntiles][bpad] for this step
-  int tile_force;  // see dense_tile
-  // BF16X3 skinny and 128 x 128 blocks: A and V_k packed in the MFMA lane layout
-  // (launch_dense_pack_*), V_new packed by the epilogue; null = unpacked
+  DenseTile tile;  // of dense_tile
+  // Skinny blocks, and BF16X3's 128 x 128 ones: A and V_k packed in the MFMA
+  // lane layout (launch_dense_pack_*), V_new packed by the epilogue; null =
+  // unpacked.  FP32 and FP64 use the hi pointers alone.
   const void* pk_a_hi = nullptr;
   const void* pk_a_lo = nullptr;
   const void* pk_v_hi = nullptr;
@@ -482,21 +487,23 @@ struct DenseStepArgs {
   void* pk_o_hi = nullptr;
   void* pk_o_lo = nullptr;
 };
-struct DenseTile {
-  bool large;
-  bool skinny;  // split-K kernel: bm probes x 16 matrix rows per workgroup
-  int bm, bn;
-};
 // force: -1 = default rule, 0 = 32 x 32, 1 = 128 x 128, 2 = 64 x 64 tiles,
-// 3 = skinny (each when the block and the row alignment allow it)
-DenseTile dense_tile(int prec, int64_t d, int64_t lda, int64_t bpad, int force = -1);
+// 3 = skinny (each when the block and the row alignment allow it); packed:
+// packed operands are at hand, or will be if the tile uses them; same_sums: the
+// order of the block's sums is that of row-major operands
+DenseTile dense_tile(int prec, int64_t d, int64_t lda, int64_t bpad, bool packed, bool same_sums,
+                     int force = -1);
 hipError_t launch_dense_step(hipStream_t s, int prec, const DenseStepArgs& a);
 hipError_t launch_dense_probe_init(hipStream_t s, int prec, void* v0, int64_t d, int64_t bpad,
                                    ProbeSrc src, double* dots0);
-// Packed operands of the skinny BF16X3 kernel: bytes of one part (hi or lo)
-// for rows x d, and the packing of A's bf16 split (d x d, row-major) and of
-// an FP32 probe block (rows x d, probe-major).
-size_t dense_pack_bytes(int64_t rows, int64_t d);
+// Packed operands: bytes for rows x d (BF16X3: of one part, hi or lo); FP32 /
+// FP64: matrix and V_0 into the packed layout, zeros into the second packed
+// block; BF16X3: the packing of A's bf16 split (d x d, row-major) and of an
+// FP32 probe block (rows x d, probe-major).
+size_t dense_pack_bytes(int prec, int64_t rows, int64_t d);
+hipError_t launch_dense_pack_plain(hipStream_t s, int prec, const void* mat, int64_t lda,
+                                   const void* v, int64_t bpad, int64_t d, void* out_a,
+                                   void* out_v, void* zero_v);
 hipError_t launch_dense_pack_a(hipStream_t s, const void* hi, const void* lo, int64_t d,
                                void* out_hi, void* out_lo);
 hipError_t launch_dense_pack_v(hipStream_t s, const float* v, int64_t rows, int64_t d,

@@ -18,6 +18,8 @@
 //                  V_hi A_hi + V_hi A_lo + V_lo A_hi, FP32 accumulation;
 //                  A is split once (A_hi = bf16(A), A_lo = bf16(A - A_hi)),
 //                  V is split on the way into LDS.
+#include <algorithm>
+
 #include "device.hpp"
 
 namespace mlct {
@@ -28,24 +30,46 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
-// Packed bf16 operands of the skinny BF16x3 kernel.  A (rows x d) is cut
-// into tiles of 16 rows and k blocks of 32 columns; block (t, kb) holds the
-// 64 lanes' operands of one 16x16x32 MFMA in lane order, 8 values per lane:
-// lane l = (row % 16) + 16 g carries columns kb*32 + 8 g .. + 7.  Rows and
-// columns past the matrix are zero.  The same layout serves a probe block
-// (rows = probes) and the matrix (rows = matrix rows).
-__host__ __device__ inline int64_t pk_kblocks(int64_t d) { return (d + 31) / 32; }
+// Packed operands.  A matrix of rows x d values is cut into tiles of 16 rows
+// and k blocks of 4 E columns, E = 16 bytes of values (8 in bf16, 4 in FP32, 2
+// in FP64); block (t, kb) holds the 64 lanes' operands of the block's MFMAs in
+// lane order, E values per lane: lane l = (row % 16) + 16 g carries columns
+// kb * 4 E + E g .. + E - 1; in FP32 four blocks make a chunk of 64 columns, of
+// which lane group g carries columns 16 g .. + 15, four to a block: the
+// order in which the row-major kernel takes them.  (One 16x16x32 MFMA in bf16; E 16x16x4 MFMAs in
+// FP32 and FP64, the t-th on the lanes' t-th values: which columns share a k
+// slot is free as long as both operands agree.)  Rows and columns past the
+// matrix are zero.  The same layout serves a probe block (rows = probes) and
+// the matrix (rows = matrix rows).
+template <typename T>
+constexpr int kPackE = 16 / (int)sizeof(T);
+template <typename T>
+constexpr int pk_chunk = std::is_same<T, float>::value ? 4 : 1;  // blocks per chunk
+template <typename T>
+__host__ __device__ inline int64_t pk_kblocks(int64_t d) {
+  constexpr int Q = pk_chunk<T>;
+  return (d + 4 * kPackE<T> * Q - 1) / (4 * kPackE<T> * Q) * Q;
+}
+// column of value e of lane group g in block kb
+template <typename T>
+__host__ __device__ inline int64_t pk_column(int64_t kb, int64_t g) {
+  constexpr int E = kPackE<T>, Q = pk_chunk<T>;
+  return kb / Q * (4 * E * Q) + g * (E * Q) + kb % Q * E;
+}
+template <typename T>
 __host__ __device__ inline int64_t pk_index(int64_t row, int64_t k, int64_t kblocks) {
-  const int64_t lane = (row & 15) + 16 * ((k & 31) >> 3);
-  return (((row >> 4) * kblocks + (k >> 5)) * 64 + lane) * 8 + (k & 7);
+  constexpr int E = kPackE<T>, Q = pk_chunk<T>;
+  const int64_t c = k / (4 * E * Q), in = k % (4 * E * Q);
+  const int64_t kb = c * Q + in % (E * Q) / E, lane = (row & 15) + 16 * (in / (E * Q));
+  return (((row >> 4) * kblocks + kb) * 64 + lane) * E + k % E;
 }
 struct PackedOps {
-  const bf8* a_hi;  // matrix, packed
-  const bf8* a_lo;
-  const bf8* v_hi;  // V_k, packed
-  const bf8* v_lo;
-  __bf16* o_hi;     // V_new, packed (written by the epilogue)
-  __bf16* o_lo;
+  const void* a_hi;  // matrix, packed (FP32 and FP64: the values themselves)
+  const void* a_lo;
+  const void* v_hi;  // V_k, packed
+  const void* v_lo;
+  void* o_hi;        // V_new, packed (written by the epilogue)
+  void* o_lo;
 };
 
 template <int PREC>
@@ -338,7 +362,7 @@ __global__ __launch_bounds__(256) void dense_pk_gemm_kernel(
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int64_t KB = pk_kblocks(d);
+  const int64_t KB = pk_kblocks<__bf16>(d);
   // this thread's 8 pieces of a stage: piece e = tid + 256 u, decoded as
   // (which, part, tile, lane) in the order of the stage layout
   const bf8* src_of[8];
@@ -346,7 +370,8 @@ __global__ __launch_bounds__(256) void dense_pk_gemm_kernel(
   for (int u = 0; u < 8; ++u) {
     const int e = tid + 256 * u;
     const int l = e & 63, t = (e >> 6) & 7, prt = (e >> 9) & 1, which = e >> 10;
-    const bf8* base = which == 0 ? (prt ? pk.v_lo : pk.v_hi) : (prt ? pk.a_lo : pk.a_hi);
+    const bf8* base = static_cast<const bf8*>(which == 0 ? (prt ? pk.v_lo : pk.v_hi)
+                                                         : (prt ? pk.a_lo : pk.a_hi));
     const int64_t tile = which == 0 ? m0 / 16 + t : n0 / 16 + t;
     src_of[u] = base + tile * KB * 64 + l;
   }
@@ -434,9 +459,9 @@ __global__ __launch_bounds__(256) void dense_pk_gemm_kernel(
         vm[idx] = vn;
         __bf16 h, lo;
         split_bf16(vn, h, lo);
-        const int64_t q = pk_index(j, n, KB);
-        pk.o_hi[q] = h;
-        pk.o_lo[q] = lo;
+        const int64_t q = pk_index<__bf16>(j, n, KB);
+        static_cast<__bf16*>(pk.o_hi)[q] = h;
+        static_cast<__bf16*>(pk.o_lo)[q] = lo;
         if (ZMODE == 0) {
           p1[a][r] += (double)xk * (double)vn;
           p2[a][r] += (double)vn * (double)vn;
@@ -483,27 +508,36 @@ __global__ __launch_bounds__(256) void dense_pk_gemm_kernel(
   }
 }
 
-// Skinny blocks (32 or 64 probes per tile).  A block-square tile would give
-// a few hundred single-wave workgroups that each walk the whole k range with
-// one load in flight, so the step would be latency-bound.  Here a workgroup
-// owns all BM probes of its tile against only 16 matrix rows, and its four
-// waves split the k range between them (split-K inside the workgroup):
-// wave w takes chunks w, w+4, ... of KC = 4E columns, each lane loading E
-// columns of its row (64 bytes of V), the next chunks prefetched into
-// registers while the current one is on the matrix cores.  No LDS staging: the MFMA
-// operands come straight from the registers the loads filled, since the
-// assignment of columns to an MFMA's k slots only has to agree between the
-// two operands.  The four partial accumulators are summed through LDS in a
-// fixed wave order, and wave a runs the epilogue of probe tile a.
+// Split-K tiles: a workgroup owns 16 TM probes against 16 TN matrix rows, and
+// its W waves split the k range between them, so that a block of few probes
+// still has a load in flight per wave and a workgroup per compute unit.  No LDS
+// staging: the MFMA operands come straight from the registers the loads
+// filled, since the assignment of columns to an MFMA's k slots only has to
+// agree between the two operands.  The W partial accumulators are summed
+// through LDS in a fixed wave order, and wave a runs the epilogue of probe
+// tile a.
 //
-// PK (BF16x3 only): both operands come pre-split and pre-packed in the lane
-// layout of the 16x16x32 bf16 MFMA (see the packed layout below), so each
-// 16-byte load of a wave covers 1 KB of contiguous memory instead of 16
-// rows' worth of scattered pieces; the epilogue writes V_new packed for the
-// next step as well.  The number of distinct cache lines per load, not the
-// bytes, bounds the unpacked form.
-template <int PREC, int TM, int W, int ZMODE, bool HAS_PREV, bool PK = false>
-__global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
+// PK: both operands come packed in the lane layout of the MFMAs (above; BF16x3
+// split as well), so each 16-byte load of a wave covers 1 KB of contiguous
+// memory instead of 16 rows' worth of scattered pieces; the epilogue writes
+// V_new packed for the next step as well.  The number of distinct cache lines
+// per load, not the bytes, bounds the unpacked form.  Measured per step at d =
+// 4096, rows -> packed: 64 probes BF16x3 42 -> 18 us, FP32 44 -> 25, FP64 77 ->
+// 41.  From some 100 probes on, the loads out of L2 bound a 64 x 16 tile (FP64
+// 16 TB/s of them at 53 TFLOP/s) and wider ones the matrix cores: FP64 512
+// probes 53 TFLOP/s on 64 x 16, 68 on 64 x 64 (128 x 128 tiles staged through
+// LDS: 40); FP32 88 and 110 (LDS: 85); BF16x3 450 and 740.
+//
+// !PK (TN = 1, row-major operands): wave w takes chunks w, w + W, ... of KC =
+// 4E columns, each lane loading E columns of its row (64 bytes of V), the next
+// chunks prefetched into registers while the current one is on the matrix
+// cores.  For calls of few steps and those without room to pack.
+// The fixed wave count of FP64's 64 x 64 tiles keeps the compiler from moving
+// all their accumulators once per loop pass (d = 4096, 1024 probes, degree 32
+// 7.95 -> 7.78 ms).
+template <int PREC, int TM, int TN, int W, int ZMODE, bool HAS_PREV, bool PK>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(
+    TN == 4 && PREC == 0 ? 2 : 1, TN == 4 && PREC == 0 ? 2 : 8))) void dense_skinny_kernel(
     const void* __restrict__ A0, const void* __restrict__ A1, int64_t lda, int64_t d,
     const typename Prec<PREC>::V* __restrict__ vk, typename Prec<PREC>::V* __restrict__ vm,
     typename Prec<PREC>::V ca, typename Prec<PREC>::V cb, ProbeSrc src, int mtiles, int ntiles,
@@ -523,7 +557,8 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
   constexpr int NSPLIT = PREC == 2 ? 2 : 1;
   typedef MT aq __attribute__((ext_vector_type(QA)));
   typedef VT vq __attribute__((ext_vector_type(QV)));
-  static_assert(TM <= W, "one epilogue tile per wave");
+  static_assert(TM <= W, "one epilogue row of tiles per wave");
+  static_assert(PK || TN == 1, "unpacked operands: 16 matrix rows");
 
   __shared__ AccT red[W][TM][64];
 
@@ -531,8 +566,9 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
   const int L = xcd_band(blockIdx.x, (total + 7) / 8 * 8);
   if (L >= total) return;
   const int mt = L % mtiles, nt = L / mtiles;
-  const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * (16 * TN);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, rl = lane & 15;
 
   // Rows past d read row 0: column n of the product depends on row n of A
@@ -545,16 +581,16 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
 #pragma unroll
   for (int a = 0; a < TM; ++a) vrow[a] = vk + (m0 + a * 16 + rl) * d;
 
-  // NS accumulators per probe tile, so that consecutive MFMAs of one wave
+  // NS accumulators per tile, so that consecutive MFMAs of one wave
   // are independent (a chain of dependent MFMAs issues at a fraction of the
   // matrix-core rate): bf16x3 keeps one per product (hi*hi, hi*lo, lo*hi),
   // FP32 and FP64 one per k slot modulo NS.  Summed in a fixed order.
   constexpr int NS = PREC == 2 ? 3 : (PREC == 1 ? 2 : 1);
-  AccT acc[TM][NS];
+  AccT acc[TM][TN * NS];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int q = 0; q < NS; ++q) acc[a][q] = AccT{};
+    for (int q = 0; q < TN * NS; ++q) acc[a][q] = AccT{};
 
   aq ra[NSPLIT][NA], xa[NSPLIT][NA];
   vq rv[TM][NV], xv[TM][NV];
@@ -614,50 +650,67 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
   // back into load-then-use).  Past the last chunk a load re-reads that
   // chunk (a cache hit), so every load in the loop is unconditional.
   if constexpr (PK) {
-    static_assert(PREC == 2, "packed operands are bf16 hi / lo");
-    // k blocks of 32: wave w takes blocks w, w + W, ...; two register sets
-    // in turn, as below.  Padding (k >= d, rows >= d) is zero in both.
-    const int64_t KB = pk_kblocks(d);
-    const bf8* ph = pk.a_hi + ((int64_t)nt * KB) * 64 + lane;
-    const bf8* pl = pk.a_lo + ((int64_t)nt * KB) * 64 + lane;
-    const bf8* qh = pk.v_hi + ((int64_t)(m0 / 16) * KB) * 64 + lane;
-    const bf8* ql = pk.v_lo + ((int64_t)(m0 / 16) * KB) * 64 + lane;
-    const int64_t nk = KB > wave ? (KB - wave + W - 1) / W : 0;
-    auto kbof = [&](int64_t i) { return (int64_t)wave + (i < nk ? i : nk - 1) * W; };
-    bf8 b0h, b0l, b1h, b1l, x0h[TM], x0l[TM], x1h[TM], x1l[TM];
-    auto ld = [&](int64_t kb, bf8& bh, bf8& bl, bf8 (&xh)[TM], bf8 (&xl)[TM]) {
-      bh = ph[kb * 64];
-      bl = pl[kb * 64];
+    // k blocks of 4 kPackE columns: wave w takes chunks w, w + W, ... (an odd
+    // block first, so that the loop runs over pairs).  Padding (k >= d, rows >=
+    // d) is zero in both operands.
+    typedef MT pv __attribute__((ext_vector_type(QA)));
+    const int KB = (int)pk_kblocks<MT>(d);
+    const pv *pa[NSPLIT], *pq[NSPLIT];
 #pragma unroll
-      for (int a = 0; a < TM; ++a) {
-        xh[a] = qh[(a * KB + kb) * 64];
-        xl[a] = ql[(a * KB + kb) * 64];
+    for (int h = 0; h < NSPLIT; ++h) {
+      pa[h] = static_cast<const pv*>(h ? pk.a_lo : pk.a_hi) + (int64_t)nt * TN * KB * 64 + lane;
+      pq[h] = static_cast<const pv*>(h ? pk.v_lo : pk.v_hi) + (m0 / 16) * KB * 64 + lane;
+    }
+    constexpr int Q = pk_chunk<MT>;
+    const int nk = KB / Q > wave ? (KB / Q - wave + W - 1) / W * Q : 0;
+    auto kbof = [&](int i) {
+      const int u = i < nk ? i : nk - 1;
+      return (wave + u / Q * W) * Q + u % Q;
+    };
+    pv b0[NSPLIT][TN], b1[NSPLIT][TN], x0[NSPLIT][TM], x1[NSPLIT][TM];
+    auto ld = [&](int kb, pv (&b)[NSPLIT][TN], pv (&x)[NSPLIT][TM]) {
+#pragma unroll
+      for (int h = 0; h < NSPLIT; ++h) {
+#pragma unroll
+        for (int c = 0; c < TN; ++c) b[h][c] = pa[h][(int64_t)(c * KB + kb) * 64];
+#pragma unroll
+        for (int a = 0; a < TM; ++a) x[h][a] = pq[h][(int64_t)(a * KB + kb) * 64];
       }
     };
-    auto mm = [&](const bf8& bh, const bf8& bl, const bf8 (&xh)[TM], const bf8 (&xl)[TM]) {
+    // consecutive MFMAs go to different accumulators
+    auto mm = [&](const pv (&b)[NSPLIT][TN], const pv (&x)[NSPLIT][TM]) {
 #pragma unroll
-      for (int a = 0; a < TM; ++a) {
-        acc[a][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[a], bh, acc[a][0], 0, 0, 0);
-        acc[a][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[a], bl, acc[a][1], 0, 0, 0);
-        acc[a][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl[a], bh, acc[a][2], 0, 0, 0);
-      }
+      for (int t = 0; t < (PREC == 2 ? 3 : QA); ++t)
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int c = 0; c < TN; ++c) {
+            AccT& q = acc[a][c * NS + t % NS];
+            if constexpr (PREC == 0)
+              q = __builtin_amdgcn_mfma_f64_16x16x4f64(x[0][a][t], b[0][c][t], q, 0, 0, 0);
+            else if constexpr (PREC == 1)
+              q = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][a][t], b[0][c][t], q, 0, 0, 0);
+            else
+              q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t == 2][a], b[t == 1][c], q, 0, 0, 0);
+          }
     };
     if (nk > 0) {
-      ld(kbof(0), b0h, b0l, x0h, x0l);
+      int i = nk & 1;
+      if (i) ld(kbof(0), b1, x1);
+      ld(kbof(i), b0, x0);
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
-      int64_t i = 0;
-      for (; i + 2 <= nk; i += 2) {
-        ld(kbof(i + 1), b1h, b1l, x1h, x1l);
+      if (i) mm(b1, x1);
+      for (; i < nk; i += 2) {
+        ld(kbof(i + 1), b1, x1);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        mm(b0h, b0l, x0h, x0l);
-        ld(kbof(i + 2), b0h, b0l, x0h, x0l);
+        mm(b0, x0);
+        ld(kbof(i + 2), b0, x0);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        mm(b1h, b1l, x1h, x1l);
+        mm(b1, x1);
       }
-      if (i < nk) mm(b0h, b0l, x0h, x0l);
     }
   } else {
   const int64_t nfull = d / KC;
@@ -705,51 +758,68 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
   }
   }  // unpacked operands
 
-#pragma unroll
-  for (int a = 0; a < TM; ++a) {
-    AccT t = acc[a][0];
-#pragma unroll
-    for (int q = 1; q < NS; ++q) t += acc[a][q];
-    red[wave][a][lane] = t;
-  }
-  __syncthreads();
-  if (wave >= TM) return;
-
-  // ---- epilogue of probe tile a = wave: recurrence in place, partials ----
-  const int a = wave;
-  AccT sum = red[0][a][lane];
-#pragma unroll
-  for (int w = 1; w < W; ++w) sum += red[w][a][lane];
-  const int64_t n = n0 + rl;
+  // ---- per matrix tile c: sum over the waves, then the epilogue of the tiles
+  // (a = wave, c): recurrence in place, partials summed over c ---------------
   double p1[4], p2[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    p1[r] = p2[r] = 0.0;
-    const int64_t j = m0 + a * 16 + acc_row<PREC>(lane, r);
-    if (n >= d) continue;
-    const int64_t idx = j * d + n;
-    const VT x = vk[idx];
-    VT vn = ca * (VT)sum[r] + cb * x;
-    if (HAS_PREV) vn -= vm[idx];
-    vm[idx] = vn;
-    if constexpr (PK) {
-      __bf16 h, lo;
-      split_bf16((float)vn, h, lo);
-      const int64_t q = pk_index(j, n, pk_kblocks(d));
-      pk.o_hi[q] = h;
-      pk.o_lo[q] = lo;
+  for (int r = 0; r < 4; ++r) p1[r] = p2[r] = 0.0;
+  VT xk[TN][4], xm[TN][4];  // V_k and V_{k-1}, on their way during the sums
+#pragma unroll
+  for (int c = 0; c < TN; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t n = n0 + c * 16 + rl;
+      const int64_t idx = (m0 + wave * 16 + acc_row<PREC>(lane, r)) * d + n;
+      const bool ok = wave < TM && n < d;
+      xk[c][r] = ok ? vk[idx] : VT(0);
+      xm[c][r] = HAS_PREV && ok ? vm[idx] : VT(0);
     }
-    if (ZMODE == 0) {
-      p1[r] = (double)x * (double)vn;
-      p2[r] = (double)vn * (double)vn;
-    } else if (ZMODE == 1) {
-      const uint64_t key = sm_output(src.seed, (uint64_t)(src.first_id + j));
-      p1[r] = sign_from_word<double>(sm_output(key, (uint64_t)(n >> 6)), n) * (double)vn;
-    } else {
-      const double z = j < src.active ? (double)src.entries[n * src.ld + src.first_id + j] : 0.0;
-      p1[r] = z * (double)vn;
+#pragma unroll
+  for (int c = 0; c < TN; ++c) {
+    if (c > 0) __syncthreads();
+#pragma unroll
+    for (int a = 0; a < TM; ++a) {
+      AccT t = acc[a][c * NS];
+#pragma unroll
+      for (int q = 1; q < NS; ++q) t += acc[a][c * NS + q];
+      red[wave][a][lane] = t;
+    }
+    __syncthreads();
+    const int64_t n = n0 + c * 16 + rl;
+    if (wave >= TM || n >= d) continue;
+    AccT sum = red[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) sum += red[w][wave][lane];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t j = m0 + wave * 16 + acc_row<PREC>(lane, r);
+      const int64_t idx = j * d + n;
+      const VT x = xk[c][r];
+      VT vn = ca * (VT)sum[r] + cb * x;
+      if (HAS_PREV) vn -= xm[c][r];
+      vm[idx] = vn;
+      if constexpr (PK && PREC == 2) {
+        __bf16 h, lo;
+        split_bf16((float)vn, h, lo);
+        const int64_t q = pk_index<__bf16>(j, n, pk_kblocks<__bf16>(d));
+        static_cast<__bf16*>(pk.o_hi)[q] = h;
+        static_cast<__bf16*>(pk.o_lo)[q] = lo;
+      } else if constexpr (PK) {
+        static_cast<VT*>(pk.o_hi)[pk_index<VT>(j, n, pk_kblocks<VT>(d))] = vn;
+      }
+      if (ZMODE == 0) {
+        p1[r] += (double)x * (double)vn;
+        p2[r] += (double)vn * (double)vn;
+      } else if (ZMODE == 1) {
+        const uint64_t key = sm_output(src.seed, (uint64_t)(src.first_id + j));
+        p1[r] += sign_from_word<double>(sm_output(key, (uint64_t)(n >> 6)), n) * (double)vn;
+      } else {
+        const double z = j < src.active ? (double)src.entries[n * src.ld + src.first_id + j] : 0.0;
+        p1[r] += z * (double)vn;
+      }
     }
   }
+  if (wave >= TM) return;
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -761,7 +831,7 @@ __global__ __launch_bounds__(64 * W) void dense_skinny_kernel(
     const int64_t width = (int64_t)mtiles * BM;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t j = m0 + a * 16 + acc_row<PREC>(lane, r);
+      const int64_t j = m0 + wave * 16 + acc_row<PREC>(lane, r);
       part[(int64_t)nt * width + j] = p1[r];
       part[((int64_t)ntiles + nt) * width + j] = p2[r];
     }
@@ -809,7 +879,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const ST* __restrict__ hi_or_
                                                    int64_t rp, int64_t d, int64_t ld,
                                                    __bf16* __restrict__ out_hi,
                                                    __bf16* __restrict__ out_lo) {
-  const int64_t KB = pk_kblocks(d);
+  const int64_t KB = pk_kblocks<__bf16>(d);
   const int64_t cols = KB * 32;
   const int64_t total = rp * cols;
   for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total;
@@ -824,9 +894,47 @@ __global__ __launch_bounds__(256) void pack_kernel(const ST* __restrict__ hi_or_
         l = lo[r * ld + k];
       }
     }
-    const int64_t q = pk_index(r, k, KB);
+    const int64_t q = pk_index<__bf16>(r, k, KB);
     out_hi[q] = h;
     out_lo[q] = l;
+  }
+}
+
+// The packed operands of one FP32 or FP64 block in one launch: matrix (row
+// stride lda) and V_0 into the layout of their type, zero past their rows and
+// columns, and zeros over the second packed block, whose padding stays zero.
+// It is written anew for every block of probes, since the matrix belongs to
+// the caller, who may change it between calls: d = 4096 in FP32 adds 30 us to
+// steps that each save 18 at 64 probes.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_plain_kernel(
+    const T* __restrict__ mat, int64_t lda, const T* __restrict__ v, int64_t bpad, int64_t d,
+    int64_t rp_a, int64_t rp_v, T* __restrict__ out_a, T* __restrict__ out_v,
+    T* __restrict__ zero_v) {
+  constexpr int E = kPackE<T>;
+  typedef T pv __attribute__((ext_vector_type(E)));
+  const int64_t KB = pk_kblocks<T>(d);
+  const int64_t na = rp_a / 16 * KB * 64, nv = rp_v / 16 * KB * 64;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < na + 2 * nv;
+       i += (int64_t)gridDim.x * 256) {
+    pv x;
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = T(0);
+    if (i >= na + nv) {
+      reinterpret_cast<pv*>(zero_v)[i - na - nv] = x;
+      continue;
+    }
+    const bool of_v = i >= na;
+    const int64_t t = of_v ? i - na : i;
+    const int64_t lane = t & 63, blk = t >> 6;
+    const int64_t row = blk / KB * 16 + (lane & 15), k = pk_column<T>(blk % KB, lane >> 4);
+    const T* src = of_v ? v + row * d : mat + row * lda;
+    if (row < (of_v ? bpad : d)) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (k + e < d) x[e] = src[k + e];
+    }
+    reinterpret_cast<pv*>(of_v ? out_v : out_a)[t] = x;
   }
 }
 
@@ -989,26 +1097,19 @@ hipError_t launch_dense_cfg(hipStream_t s, const DenseStepArgs& a) {
   return hipGetLastError();
 }
 
-template <int PREC, int TM, int W>
+template <int PREC, int TM, int TN, int W, bool PK>
 hipError_t launch_skinny_cfg(hipStream_t s, const DenseStepArgs& a) {
   using VT = typename Prec<PREC>::V;
   const int mtiles = (int)(a.bpad / (TM * 16));
-  const int ntiles = (int)((a.d + 15) / 16);
+  const int ntiles = (int)((a.d + 16 * TN - 1) / (16 * TN));
   const int grid = (mtiles * ntiles + 7) / 8 * 8;
   const VT ca = (VT)a.ca, cb = (VT)a.cb;
   const VT* vk = static_cast<const VT*>(a.vk);
   VT* vm = static_cast<VT*>(a.vm);
-  const PackedOps pk{static_cast<const bf8*>(a.pk_a_hi), static_cast<const bf8*>(a.pk_a_lo),
-                     static_cast<const bf8*>(a.pk_v_hi), static_cast<const bf8*>(a.pk_v_lo),
-                     static_cast<__bf16*>(a.pk_o_hi), static_cast<__bf16*>(a.pk_o_lo)};
-  const bool packed = PREC == 2 && a.pk_a_hi != nullptr;
+  const PackedOps pk{a.pk_a_hi, a.pk_a_lo, a.pk_v_hi, a.pk_v_lo, a.pk_o_hi, a.pk_o_lo};
 #define MLCT_SKINNY_LAUNCH(Z, HP)                                                             \
-  if (packed)                                                                                 \
-    dense_skinny_kernel<PREC, TM, W, Z, HP, PREC == 2><<<grid, 64 * W, 0, s>>>(                \
-        a.A0, a.A1, a.lda, a.d, vk, vm, ca, cb, a.src, mtiles, ntiles, a.part, pk);            \
-  else                                                                                        \
-    dense_skinny_kernel<PREC, TM, W, Z, HP><<<grid, 64 * W, 0, s>>>(                           \
-        a.A0, a.A1, a.lda, a.d, vk, vm, ca, cb, a.src, mtiles, ntiles, a.part, pk)
+  dense_skinny_kernel<PREC, TM, TN, W, Z, HP, PK><<<grid, 64 * W, 0, s>>>(                     \
+      a.A0, a.A1, a.lda, a.d, vk, vm, ca, cb, a.src, mtiles, ntiles, a.part, pk)
   if (a.has_prev) {
     if (a.zmode == 0) MLCT_SKINNY_LAUNCH(0, true);
     else if (a.zmode == 1) MLCT_SKINNY_LAUNCH(1, true);
@@ -1026,9 +1127,7 @@ hipError_t launch_skinny_cfg(hipStream_t s, const DenseStepArgs& a) {
 hipError_t launch_pk_gemm(hipStream_t s, const DenseStepArgs& a) {
   const int mtiles = (int)(a.bpad / 128), ntiles = (int)((a.d + 127) / 128);
   const int grid = (mtiles * ntiles + 7) / 8 * 8;
-  const PackedOps pk{static_cast<const bf8*>(a.pk_a_hi), static_cast<const bf8*>(a.pk_a_lo),
-                     static_cast<const bf8*>(a.pk_v_hi), static_cast<const bf8*>(a.pk_v_lo),
-                     static_cast<__bf16*>(a.pk_o_hi), static_cast<__bf16*>(a.pk_o_lo)};
+  const PackedOps pk{a.pk_a_hi, a.pk_a_lo, a.pk_v_hi, a.pk_v_lo, a.pk_o_hi, a.pk_o_lo};
   const float* vk = static_cast<const float*>(a.vk);
   float* vm = static_cast<float*>(a.vm);
   const float ca = (float)a.ca, cb = (float)a.cb;
@@ -1050,18 +1149,15 @@ hipError_t launch_pk_gemm(hipStream_t s, const DenseStepArgs& a) {
 
 }  // namespace
 
-DenseTile dense_tile(int prec, int64_t d, int64_t lda, int64_t bpad, int force) {
-  // Blocks of at most 64 probes (512 for BF16x3) take the skinny split-K
-  // kernel (16-row tiles) when rows are 16-byte aligned.  Otherwise the largest square tile
-  // that still gives a few hundred workgroups: 128 x 128, then 64 x 64; a
-  // problem too small for either takes the skinny kernel over several probe
-  // tiles (it splits k over four waves: FP64 d = 512, 256 probes, degree 64
-  // in 0.61 ms against 1.52 ms on 32 x 32 tiles, d = 2048 2.8 vs 5.2 ms),
-  // else 32 x 32.
+DenseTile dense_tile(int prec, int64_t d, int64_t lda, int64_t bpad, bool packed, bool same_sums,
+                     int force) {
   // force: 0 = 32, 1 = 128, 2 = 64, 3 = skinny (when the block allows it).
-  // the skinny kernel's 16-byte loads need 16-byte aligned rows of V and A
+  // Packed operands take any size; row-major ones need 16-byte aligned rows of
+  // V and A for the skinny kernel's loads.
+  // same_sums: the block's sums keep the order they have on row-major operands,
+  // so the kernel is picked as there.
   const int qv = prec == MLCT_FP64 ? 2 : 4, qa = prec == MLCT_FP64 ? 2 : (prec == MLCT_FP32 ? 4 : 8);
-  const bool skinny_ok = d % qv == 0 && lda % qa == 0;
+  const bool skinny_ok = (packed && !same_sums) || (d % qv == 0 && lda % qa == 0);
   const int64_t n128 = (bpad / 128) * ((d + 127) / 128);
   const int64_t n64 = (bpad / 64) * ((d + 63) / 64);
   DenseTile t;
@@ -1070,36 +1166,80 @@ DenseTile dense_tile(int prec, int64_t d, int64_t lda, int64_t bpad, int force) 
   if (force == 3 && skinny_ok) t.skinny = true;
   else if (force == 1 && bpad % 128 == 0) size = 128;
   else if (force == 2 && bpad % 64 == 0) size = 64;
-  else if (force < 0) {
-    // BF16x3 reads packed operands on the skinny kernel, which beats square
-    // tiles up to 512 probes (d = 4096: 69 vs 124 us at 320, 108 vs 119 at
-    // 512); FP64 and FP32 read row-major arrays and keep it to 64
-    const int64_t skinny_max = prec == MLCT_BF16X3 ? 512 : 64;
-    if (bpad <= skinny_max && skinny_ok) t.skinny = true;
+  else if (force < 0 && packed && !same_sums) {
+    // Packed: the split-K kernel, at every width (d = 4096, 2048 probes, degree
+    // 32: FP64 15.6 ms against 26.2 on 128 x 128 tiles staged through LDS; FP32
+    // 9.6 against 9.9; d = 8192, 1024 probes 18.4 against 19.1).
+    t.skinny = true;
+  } else if (force < 0) {
+    // The skinny kernel up to 64 probes (BF16x3 on packed operands up to 512: d
+    // = 4096 69 vs 124 us at 320, 108 vs 119 at 512); beyond, the largest square
+    // tile that still gives a few hundred workgroups; a problem too small for
+    // either takes the skinny kernel over several probe tiles (FP64 d = 512,
+    // 256 probes, degree 64 in 0.61 ms against 1.52 ms on 32 x 32 tiles, d =
+    // 2048 2.8 vs 5.2 ms), else 32 x 32.
+    if (bpad <= (packed && prec == MLCT_BF16X3 ? 512 : 64) && skinny_ok) t.skinny = true;
     else if (bpad % 128 == 0 && n128 >= 256) size = 128;
     else if (bpad % 64 == 0 && n64 >= 256) size = 64;
     else if (skinny_ok) t.skinny = true;
   }
   if (t.skinny) {
-    t.large = false;
     t.bm = bpad % 64 == 0 ? 64 : 32;
     t.bn = 16;
+    if (packed) {
+      // Probes x matrix rows of a workgroup: the shape with the least (rounds
+      // of one workgroup per compute unit) x (time of a round, relative to 64
+      // x 64).  Large tiles load less per product (a 64 x 16 tile has a
+      // quarter of the products of 64 x 64 and takes 0.29 of its time in FP64,
+      // 0.5 in BF16x3), small ones leave fewer units idle: FP64 d = 4096, 256
+      // probes 2.1 ms on 64 x 64 (256 workgroups), 2.6 on 64 x 16; d = 2048,
+      // 64 probes 0.29 ms on 32 x 16 (256), 0.42 on 64 x 16, 0.63 on 64 x 32.
+      constexpr int kShapes[5][2] = {{64, 64}, {64, 32}, {64, 16}, {32, 16}, {16, 16}};
+      constexpr double kRound[3][5] = {{1.0, 0.53, 0.285, 0.16, 0.09},   // FP64
+                                       {1.0, 0.60, 0.31, 0.17, 0.095},   // FP32
+                                       {1.0, 0.70, 0.50, 0.33, 0.20}};   // BF16x3
+      const int p = prec == MLCT_FP64 ? 0 : prec == MLCT_FP32 ? 1 : 2;
+      double best = 0.0;
+      for (int q = 0; q < 5; ++q) {
+        const int bm = kShapes[q][0], bn = kShapes[q][1];
+        if (bpad % bm) continue;
+        const int64_t rounds = (bpad / bm * ((d + bn - 1) / bn) + 255) / 256;
+        const double cost = (double)rounds * kRound[p][q];
+        if (best > 0.0 && cost >= best) continue;
+        best = cost;
+        t.bm = bm;
+        t.bn = bn;
+      }
+    }
     return t;
   }
-  t.large = size == 128;
   t.bm = t.bn = size;
   return t;
 }
 
+// Waves that split k: 8 in FP64 (d = 4096, 64 probes 0.72 ms against 0.90 on 4;
+// d = 512, 64 probes 0.15 vs 0.17), but 4 on its 64 x 64 tiles (4096, 1024
+// probes 8.0 vs 8.2 ms); 4 in FP32 and BF16x3 (8 gain up to 10% on small blocks
+// in FP32, but change the order of the sums).
+template <int PREC>
+hipError_t launch_skinny(hipStream_t s, const DenseStepArgs& a, int bm, int bn) {
+  if (!a.pk_a_hi)
+    return bm == 64 ? launch_skinny_cfg<PREC, 4, 1, 4, false>(s, a)
+                    : launch_skinny_cfg<PREC, 2, 1, 4, false>(s, a);
+  constexpr int W = PREC == 0 ? 8 : 4;
+  if (bn == 64) return launch_skinny_cfg<PREC, 4, 4, 4, true>(s, a);
+  if (bn == 32) return launch_skinny_cfg<PREC, 4, 2, W, true>(s, a);
+  if (bm == 64) return launch_skinny_cfg<PREC, 4, 1, W, true>(s, a);
+  if (bm == 32) return launch_skinny_cfg<PREC, 2, 1, W, true>(s, a);
+  return launch_skinny_cfg<PREC, 1, 1, W, true>(s, a);
+}
+
 hipError_t launch_dense_step(hipStream_t s, int prec, const DenseStepArgs& a) {
-  const DenseTile t = dense_tile(prec, a.d, a.lda, a.bpad, a.tile_force);
+  const DenseTile t = a.tile;
   if (t.skinny) {
-    constexpr int W = 4;
-    if (prec == MLCT_FP64)
-      return t.bm == 64 ? launch_skinny_cfg<0, 4, W>(s, a) : launch_skinny_cfg<0, 2, W>(s, a);
-    if (prec == MLCT_FP32)
-      return t.bm == 64 ? launch_skinny_cfg<1, 4, W>(s, a) : launch_skinny_cfg<1, 2, W>(s, a);
-    return t.bm == 64 ? launch_skinny_cfg<2, 4, W>(s, a) : launch_skinny_cfg<2, 2, W>(s, a);
+    if (prec == MLCT_FP64) return launch_skinny<0>(s, a, t.bm, t.bn);
+    if (prec == MLCT_FP32) return launch_skinny<1>(s, a, t.bm, t.bn);
+    return launch_skinny<2>(s, a, t.bm, t.bn);
   }
   if (prec == MLCT_FP64) {
     if (t.bm == 128) return launch_dense_cfg<0, 2, 2, 4, 4, 16>(s, a);
@@ -1142,8 +1282,27 @@ hipError_t launch_dense_split(hipStream_t s, const void* a, int dtype, int64_t d
 // Packed rows are padded to a multiple of 128 (the wide kernel's tile).
 static int64_t pk_rows(int64_t rows) { return (rows + 127) / 128 * 128; }
 
-size_t dense_pack_bytes(int64_t rows, int64_t d) {
-  return (size_t)(pk_rows(rows) / 16) * (size_t)pk_kblocks(d) * 64 * 8 * sizeof(__bf16);
+size_t dense_pack_bytes(int prec, int64_t rows, int64_t d) {
+  const int64_t kb = prec == MLCT_FP64   ? pk_kblocks<double>(d)
+                     : prec == MLCT_FP32 ? pk_kblocks<float>(d)
+                                         : pk_kblocks<__bf16>(d);
+  return (size_t)(pk_rows(rows) / 16) * (size_t)kb * 64 * 16;
+}
+
+hipError_t launch_dense_pack_plain(hipStream_t s, int prec, const void* mat, int64_t lda,
+                                   const void* v, int64_t bpad, int64_t d, void* out_a,
+                                   void* out_v, void* zero_v) {
+  const size_t bytes = dense_pack_bytes(prec, d, d) + 2 * dense_pack_bytes(prec, bpad, d);
+  const int grid = (int)std::min<size_t>((bytes / 16 + 255) / 256, 8192);
+  auto go = [&](auto t) {
+    using T = decltype(t);
+    pack_plain_kernel<T><<<grid, 256, 0, s>>>(
+        static_cast<const T*>(mat), lda, static_cast<const T*>(v), bpad, d, pk_rows(d),
+        pk_rows(bpad), static_cast<T*>(out_a), static_cast<T*>(out_v), static_cast<T*>(zero_v));
+  };
+  if (prec == MLCT_FP64) go(0.0);
+  else go(0.f);
+  return hipGetLastError();
 }
 
 hipError_t launch_dense_pack_a(hipStream_t s, const void* hi, const void* lo, int64_t d,
