@@ -296,7 +296,7 @@ def extra_triangles(mlct, dev):
     out = {"workload": f"triangles, Chung-Lu d=1e6 nnz={g.nnz}, 1024 probes, int32/int64",
            "probe_matvecs_per_s": 2 * 1024 / dt, "ms": dt * 1e3, "estimate": res["estimate"],
            "estimate_cv": res["estimate_cv"],
-           "roofline": {"bound": "hbm", "kernel": "tri_step_kernel", "achieved": ach,
+           "roofline": {"bound": "hbm", "kernel": "tri_pass1_kernel + tri_pass2_kernel", "achieved": ach,
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
                         "traffic": traffic, "algorithmic_bytes_per_launch": by,
                         "avg_launch_ms": ms / n, "launches": n,
