@@ -292,15 +292,14 @@ def extra_triangles(mlct, dev):
     # y, writes nothing: the average of the two per launch
     by = 4 * g.nnz + 4 * (g.d + 1) + 6 * g.d * 64
     ach = by / (ms / n / 1e3) / 1e9
-    traffic = stored_traffic("tri_step_chunglu_1e6")
     out = {"workload": f"triangles, Chung-Lu d=1e6 nnz={g.nnz}, 1024 probes, int32/int64",
            "probe_matvecs_per_s": 2 * 1024 / dt, "ms": dt * 1e3, "estimate": res["estimate"],
            "estimate_cv": res["estimate_cv"],
-           "roofline": {"bound": "hbm", "kernel": "tri_pass1_kernel + tri_pass2_kernel", "achieved": ach,
+           "roofline": {"bound": "hbm", "kernel": "tri_pass1_kernel + tri_pass2_kernel",
+                        "achieved": ach,
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
-                        "traffic": traffic, "algorithmic_bytes_per_launch": by,
-                        "avg_launch_ms": ms / n, "launches": n,
-                        "traffic_rate_GBs": traffic / (ms / n / 1e3) / 1e9 if traffic else None}}
+                        "traffic": None, "algorithmic_bytes_per_launch": by,
+                        "avg_launch_ms": ms / n, "launches": n, "traffic_rate_GBs": None}}
     op.close()
     ctx.close()
     return out
@@ -339,14 +338,13 @@ def extra_estrada(mlct, dev):
     vec = 4 * 64 * g.d
     by = 4 * g.nnz + 4 * (g.d + 1) + 2 * vec + vec * (n - blocks) / n  # pattern: no values
     ach = by / (ms / n / 1e3) / 1e9
-    # counted HBM bytes of a V_prev-reading step: the step kernel and its hub chunks
-    t_step, t_hub = stored_traffic("csr_step_pattern_chunglu_1e6"), stored_traffic("csr_hub_chunglu_1e6")
-    traffic = t_step + t_hub if t_step and t_hub else None
+    # counted HBM bytes of a V_prev-reading step
+    traffic = stored_traffic("csr_step_pattern_chunglu_1e6")
     out = {"workload": f"Estrada index, Chung-Lu d=1e6 nnz={g.nnz}, Lanczos interval (64 steps), "
                        "levels 10/30/60, probes 768/192/64, doubling, FP32",
            "bounds_ms": tb * 1e3, "estimate_ms": te * 1e3, "interval": [a, b],
            "value": r["value"], "probe_degree_per_s": r["probe_degrees"] / te,
-           "roofline": {"bound": "hbm", "kernel": "csr_step_kernel<float,pattern,...> + hub chunks",
+           "roofline": {"bound": "hbm", "kernel": "csr_step_long_kernel<float,pattern,...>",
                         "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": ach / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": by,
                         "avg_launch_ms": ms / n, "launches": n, "traffic": traffic,
