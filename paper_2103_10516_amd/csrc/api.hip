@@ -2361,9 +2361,10 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
     }
     const bool pat = it.op->csr.val == nullptr;
     // row-length class: straight-line gathers up to 4 / 5 / 8 entries, or
-    // 9 = longer rows present
+    // 9 = rows of any length (an operator without entries among them: the
+    // straight-line form loads a column for every group of rows)
     const int mxr = it.op->csr.max_row_nnz;
-    const int mz = mxr <= 4 ? 4 : mxr <= 5 ? 5 : mxr <= 8 ? 8 : 9;
+    const int mz = it.op->csr.nnz < 1 ? 9 : mxr <= 4 ? 4 : mxr <= 5 ? 5 : mxr <= 8 ? 8 : 9;
     int var = -1;
     for (size_t v = 0; v < variants.size(); ++v)
       if (variants[v] == std::make_pair(pat, mz)) var = (int)v;
