@@ -654,9 +654,10 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
     const int32_t* t = &h[3 * (size_t)order[k]];
     rows[k] = t[0];
     c0[k] = (int32_t)cs.size();
-    for (int32_t a = t[1]; a < t[2]; a += kHubChunk) {
-      cs.push_back(a);
-      ce.push_back(std::min<int32_t>(a + kHubChunk, t[2]));
+    // (64 bits: a row may end at INT32_MAX)
+    for (int64_t a = t[1]; a < t[2]; a += kHubChunk) {
+      cs.push_back((int32_t)a);
+      ce.push_back((int32_t)std::min<int64_t>(a + kHubChunk, t[2]));
       cr.push_back(t[0]);
     }
   }

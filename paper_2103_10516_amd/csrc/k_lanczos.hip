@@ -51,7 +51,10 @@ __global__ __launch_bounds__(256) void lz_hub_chunk_kernel(const int32_t* __rest
   if (c >= nchunks) return;
   const int lane = threadIdx.x & 63;
   double s = 0.0;
-  for (int t = cs[c] + lane; t < ce[c]; t += 64) s += (val ? (double)val[t] : 1.0) * q[col[t]];
+  // (64-bit entries: the last chunk may end at INT32_MAX)
+  const int64_t e = ce[c];
+  for (int64_t t = (int64_t)cs[c] + lane; t < e; t += 64)
+    s += (val ? (double)val[t] : 1.0) * q[col[t]];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   if (lane == 0) out[c] = s;
 }
@@ -78,26 +81,32 @@ __global__ __launch_bounds__(kT) void lz_spmv_kernel(
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t i0 = wave * kWaveRows; i0 < d; i0 += nw * kWaveRows) {  // uniform over the wave
-    int64_t i[kRowSets];
-    int t[kRowSets], t1[kRowSets];
+    // t counts from the row's start: a finished row's goes on by up to
+    // kHubLen + 32 while others of the wave have entries, and its start may lie
+    // near INT32_MAX
+    int64_t i[kRowSets], t0[kRowSets];
+    int t[kRowSets], len[kRowSets];
     double s[kRowSets];
     bool hub[kRowSets];
 #pragma unroll
     for (int r = 0; r < kRowSets; ++r) {
       i[r] = i0 + r * (64 / kRowLanes) + lane / kRowLanes;
       s[r] = 0.0;
-      t[r] = t1[r] = 0;
+      t0[r] = 0;
+      len[r] = 0;
       if (i[r] < d) {
-        t[r] = rowptr[i[r]];
-        t1[r] = rowptr[i[r] + 1];
+        const int b = rowptr[i[r]];
+        t0[r] = b;
+        len[r] = rowptr[i[r] + 1] - b;
       }
-      hub[r] = hub_n > 0 && t1[r] - t[r] > kHubLen;
-      t[r] = hub[r] ? t1[r] : t[r] + sub;
+      hub[r] = hub_n > 0 && len[r] > kHubLen;
+      if (hub[r]) len[r] = 0;
+      t[r] = sub;
     }
     while (true) {
       bool more = false;
 #pragma unroll
-      for (int r = 0; r < kRowSets; ++r) more |= t[r] < t1[r];
+      for (int r = 0; r < kRowSets; ++r) more |= t[r] < len[r];
       if (!__any(more)) break;
       int c[kRowSets][kGather];
       double v[kRowSets][kGather];
@@ -106,9 +115,9 @@ __global__ __launch_bounds__(kT) void lz_spmv_kernel(
 #pragma unroll
         for (int u = 0; u < kGather; ++u) {
           const int e = t[r] + u * kRowLanes;
-          const bool in = e < t1[r];
-          c[r][u] = in ? col[e] : -1;
-          v[r][u] = in && val ? (double)val[e] : 1.0;
+          const bool in = e < len[r];
+          c[r][u] = in ? col[t0[r] + e] : -1;
+          v[r][u] = in && val ? (double)val[t0[r] + e] : 1.0;
         }
 #pragma unroll
       for (int r = 0; r < kRowSets; ++r) {

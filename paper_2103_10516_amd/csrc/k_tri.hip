@@ -106,11 +106,12 @@ __global__ __launch_bounds__(256) void tri_sym_kernel(const int32_t* __restrict_
   for (int64_t u = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); u < d + chunks; u += nslot) {
     const bool row = u < d;
     const uint64_t i = row ? (uint64_t)u : (uint64_t)hubs.cr[u - d];
-    const int b = row ? rowptr[u] : hubs.cs[u - d];
-    int e = row ? rowptr[u + 1] : hubs.ce[u - d];
-    if (row && e - b > kHubLen) e = b;
-    for (int t = b + (int)(threadIdx.x & 15); t < e; t += 16) {
-      const uint64_t j = (uint64_t)(uint32_t)col[t];
+    // (64-bit entries: the last row may end at INT32_MAX)
+    const int64_t b = row ? rowptr[u] : hubs.cs[u - d];
+    int n = (int)((row ? rowptr[u + 1] : hubs.ce[u - d]) - b);
+    if (row && n > kHubLen) n = 0;
+    for (int t = (int)(threadIdx.x & 15); t < n; t += 16) {
+      const uint64_t j = (uint64_t)(uint32_t)col[b + t];
       s += sm_mix((i << 32 | j) + kGamma) - sm_mix((j << 32 | i) + kGamma);
     }
   }
