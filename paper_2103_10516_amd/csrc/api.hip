@@ -787,9 +787,9 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
 
 // The tile of a block of bpad probes with S steps, and whether it reads packed
 // operands, whose workspace (WS_DPACK) is taken here.  FP32 and FP64 pack
-// matrix and probes anew for each block, which a few steps have to pay for
-// (d = 4096, 64 probes in FP32: 30 us once against 18 us a step).  Where there
-// is no memory for packed operands, the block goes without.
+// matrix and probes anew for each block, which its steps have to pay for
+// (dense_pack_steps).  Where there is no memory for packed operands, the block
+// goes without.
 //
 // BF16X3 and the FP32 blocks of a Gram operator keep the order of their sums:
 // another order makes neither of them more exact, since the split's and the
@@ -797,14 +797,28 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
 // come out as near or nearer: d = 2048, degree 48, 700 probes 2.1e-6 -> 0.8e-6),
 // but it moves BF16X3 moments of a small operator by as much as the split's
 // error (d = 100, 40 probes: 4e-5), and the variances of nuclear norms by 1e-6.
-constexpr int kPackMinSteps = 4;
 constexpr size_t kMaxPack = (size_t)8 << 30;
+
+// The least steps for which an FP32 or FP64 block is packed.  At d = 4096, 64
+// probes in FP32, packing takes 30 us and saves 18 a step; on small matrices it
+// is a launch of 10 us and a step saves 1 to 2 (symmetric form, one call, rows ->
+// packed: FP64 d = 64, one probe 67 -> 76 us at 4 steps, 98 -> 98 at 10; 64
+// probes 91 -> 87 at 7; 256 probes 87 -> 85 at 5; FP64 d = 96, one probe 66 ->
+// 79 at 4, 75 -> 65 at 5; d = 128 71 -> 65 at 4; FP32 d = 128, one probe 71 ->
+// 78 at 4, 106 -> 105 at 10; d = 200 65 -> 62 at 4).
+int dense_pack_steps(int prec, int64_t d, int64_t bpad) {
+  if (d >= (prec == MLCT_FP64 ? 128 : 160)) return 4;
+  if (prec == MLCT_FP64 && d >= 96) return 5;
+  return bpad <= 32 ? 10 : bpad < 128 ? 7 : 5;
+}
+
 mlct_status dense_shape(mlct_ctx* ctx, const mlct_op* op, int prec, int64_t lda, int64_t bpad,
                         int S, DenseTile* t, bool* packed) {
   const int choice = dense_choice(ctx, op, prec, bpad);
   const size_t pa = dense_pack_bytes(prec, op->d, op->d), pv = dense_pack_bytes(prec, bpad, op->d);
   const bool same_sums = prec == MLCT_BF16X3 || (prec == MLCT_FP32 && op->kind == OP_GRAM);
-  *packed = prec == MLCT_BF16X3 || (S >= kPackMinSteps && pa + 2 * pv <= kMaxPack);
+  *packed = prec == MLCT_BF16X3 ||
+            (S >= dense_pack_steps(prec, op->d, bpad) && pa + 2 * pv <= kMaxPack);
   if (*packed) {
     *t = dense_tile(prec, op->d, lda, bpad, true, same_sums, choice);
     *packed = t->skinny || (prec == MLCT_BF16X3 && t->bm == 128);
