@@ -372,8 +372,9 @@ mlct_status mlct_lanczos(mlct_ctx* ctx, const mlct_op* op, int32_t steps, uint64
  * A CSR operator with fewer than 512 workgroups per step (about d < 131072)
  * in MLCT_FP32 runs as a one-item mlct_estimate_batch (all blocks in shared
  * launches) where that is faster: without rows longer than 256 entries from
- * four probe blocks on (three up to 8,192 rows), with them from three up to
- * 32,768 rows;
+ * four probe blocks on; three of them up to 8,192 rows, and operators with
+ * longer rows from three up to 32,768 rows, if at least three steps and a
+ * quarter of the longest block's are saved and the memory is there;
  * the result is the same bit for bit. */
 mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double a, double b,
                           const mlct_levels* levels, uint64_t seed, int32_t prec,

@@ -1447,40 +1447,6 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
     const int steps = op->d < 64 ? (int)op->d : 64;
     CHECK(mlct_bounds(ctx, op, steps, seed + kGamma, 0.01, &a, &b));
   }
-  // A CSR operator too small to fill the device with one probe block per
-  // launch (fewer than kSmallGroups workgroups per step) runs its probe blocks
-  // in shared launches (the batched path, whose results equal this function's
-  // bit for bit) when there are at least kSharedBlocks of them; fewer gain
-  // less than the batched path's set-up costs.  (Only below the batch's solo
-  // threshold, from which the batched path would hand the operator back here.)
-  // Three blocks suffice up to 8,192 rows (2D Laplacian 64^2: 353 -> 306 us; at
-  // 35,937 rows 1,840 -> 2,015).  Operators with rows longer than kHubLen go
-  // there up to 32,768 rows (graph of 20,000 vertices, four blocks: 1,884 ->
-  // 1,347 us; of 100,000: 3,719 -> 4,505).  These two take the shared launches'
-  // memory only where it is small.
-  if (op->kind == OP_CSR && prec == MLCT_FP32 && op->d < ctx->batch_solo_rows &&
-      (mode == MLCT_DIRECT || mode == MLCT_DOUBLING) && levels->L >= 1 &&
-      levels->L <= MLCT_MAX_LEVELS && levels->m && levels->degree &&
-      (uint64_t)op->d * 64 * 4 <= 0xFFFFFFFFull &&
-      plan_csr(op->d, op->tuned_groups).ngroups < kSmallGroups) {
-    int64_t blocks = 0;
-    for (int k = 0; k < levels->L; ++k)
-      blocks += levels->m[k] > 0 ? (levels->m[k] + kBlockProbes - 1) / kBlockProbes : 0;
-    const bool usual = op->csr.hub_n == 0 && blocks >= kSharedBlocks;
-    bool small = blocks >= 3 && op->d <= (op->csr.hub_n == 0 ? 8192 : 32768);
-    if (small && !usual) {
-      const int64_t top = std::max(0, levels->degree[levels->L - 1]);
-      const double each = 512.0 * op->d + 1024.0 * (plan_csr(op->d, op->tuned_groups).ngroups + 1) *
-                                              (double)(top + 1);
-      const double most =
-          ctx->ws_limit ? 0.5 * ((double)ctx->ws_limit - (double)ctx->ws_total) : 1073741824.0;
-      small = blocks * each <= most;
-    }
-    if (usual || small) {
-      const mlct_batch_item it{op, f, a, b, *levels, seed};
-      return mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, out);
-    }
-  }
   CHECK(check_func(ctx, f, a, b));
   const int L = levels->L;
   if (L < 1 || L > MLCT_MAX_LEVELS || !levels->degree || !levels->m)
@@ -1504,6 +1470,59 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
   }
   const int n = lv.degree[L - 1];
   if (n < 1) return fail(ctx, MLCT_EINVAL, "top degree must be >= 1");
+  const auto outside = [&](double ratio) {
+    return fail(ctx, MLCT_ESPECTRUM,
+                "max |mu_j|/|z|^2 = %g > 1: the spectrum is not inside [a, b] = [%g, %g]", ratio, a,
+                b);
+  };
+  // A CSR operator too small to fill the device with one probe block per
+  // launch (fewer than kSmallGroups workgroups per step) runs its probe blocks
+  // in shared launches (the batched path, whose results equal this function's
+  // bit for bit) when there are at least kSharedBlocks of them; fewer gain
+  // less than the batched path's set-up costs.  (Only below the batch's solo
+  // threshold, from which the batched path would hand the operator back here.)
+  // Three blocks suffice up to 8,192 rows, and operators with rows longer than
+  // kHubLen go there up to 32,768 rows, where the launches saved are at least a
+  // quarter of those that stay: a shared step costs up to 1.2 of a single one.
+  // us, block by block -> shared, levels 8:128,60:64 (a quarter): 2D Laplacian
+  // 1,024 rows 337 -> 323, 8,100 461 -> 438, graph of 32,768 vertices 1,413 ->
+  // 1,410; 8:128,100:64 (a sixth): 474 -> 487, 667 -> 682, 2,125 -> 2,203;
+  // 4:128,250:64: 974 -> 1,109, 1,400 -> 1,592, 4,642 -> 5,080; 20:192 (all of
+  // one length) 272 -> 163, 371 -> 206.  Past the lines: 22,500 rows 8:128,40:64
+  // 383 -> 370, 35,937 rows 1,840 -> 2,015; graph of 40,000 10:128,30:128,60:64
+  // 2,028 -> 1,950, of 50,000 2,055 -> 2,200.  These two take the shared
+  // launches' memory only where it is small, and do without when there is none.
+  if (op->kind == OP_CSR && prec == MLCT_FP32 && op->d < ctx->batch_solo_rows &&
+      (uint64_t)op->d * 64 * 4 <= 0xFFFFFFFFull &&
+      plan_csr(op->d, op->tuned_groups).ngroups < kSmallGroups) {
+    int64_t blocks = 0, steps = 0, longest = 0;
+    for (int k = 0; k < L; ++k) {
+      const int64_t nb = (lv.m[k] + kBlockProbes - 1) / kBlockProbes;
+      longest = mode == MLCT_DOUBLING ? (lv.degree[k] + 1) / 2 : lv.degree[k];
+      blocks += nb;
+      steps += nb * longest;
+    }
+    const bool usual = op->csr.hub_n == 0 && blocks >= kSharedBlocks;
+    bool small = blocks >= 3 && op->d <= (op->csr.hub_n == 0 ? 8192 : 32768) &&
+                 steps - longest >= 3 && 4 * (steps - longest) >= longest;
+    if (small && !usual) {
+      const double each = 512.0 * op->d + 1024.0 * (plan_csr(op->d, op->tuned_groups).ngroups + 1) *
+                                              (double)(n + 1);
+      const double most =
+          ctx->ws_limit ? 0.5 * ((double)ctx->ws_limit - (double)ctx->ws_total) : 1073741824.0;
+      small = blocks * each <= most;
+    }
+    const mlct_batch_item it{op, f, a, b, *levels, seed};
+    if (usual) return mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, out);
+    if (small) {
+      mlct_result h;
+      const mlct_status st = mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, &h);
+      if (st == MLCT_ESPECTRUM) return outside(h.max_moment_ratio);
+      if (st == MLCT_OK) *out = h;
+      if (st != MLCT_ENOMEM) return st;
+      ctx->err.clear();
+    }
+  }
   CHECK(set_device(ctx));
   const double alpha = 2.0 / (b - a), beta = -(a + b) / (b - a);
   if (exact_low) {
@@ -1553,10 +1572,7 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
   mlct_result h;
   HIPCHK(ctx, hipMemcpyAsync(&h, res, sizeof h, hipMemcpyDeviceToHost, s));
   CHECK(sync_stream(ctx));
-  if (!(h.max_moment_ratio <= 1.0 + 1e-3))
-    return fail(ctx, MLCT_ESPECTRUM,
-                "max |mu_j|/|z|^2 = %g > 1: the spectrum is not inside [a, b] = [%g, %g]",
-                h.max_moment_ratio, a, b);
+  if (!(h.max_moment_ratio <= 1.0 + 1e-3)) return outside(h.max_moment_ratio);
   h.matvecs = mv;
   h.probe_degrees = pd;
   h.interval_a = a;
