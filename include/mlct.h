@@ -22,7 +22,14 @@
  *    returns host results synchronises that stream before returning.
  *  - Calls on one context are not thread-safe; use one context per thread.
  *  - The library allocates its own device workspace (grow-only, owned by the
- *    context, freed by mlct_destroy).
+ *    context, freed by mlct_destroy).  One slot of it holds what only makes
+ *    calls faster: packed operands of dense blocks (matrix and probes, up to
+ *    8 GiB), triangle panels past the first (about 1 GiB at most), the shared
+ *    launches of small estimates (up to 1 GiB).  It is kept for the next call,
+ *    counts as workspace, and is given up whenever another slot or operator
+ *    needs the room.  Where it is not to be had, calls go without: results are
+ *    the same bit for bit, except that FP64, FP32 and BF16X3 blocks of a dense
+ *    matrix then sum in another order (within the precision's rounding).
  */
 #ifndef MLCT_H
 #define MLCT_H
@@ -170,7 +177,8 @@ mlct_status mlct_destroy(mlct_ctx* ctx);
 /* Text of the last error on this context ("" if none).  Owned by ctx. */
 const char* mlct_last_error(const mlct_ctx* ctx);
 /* Cap on the context's device workspace in bytes (0 = no cap).  A call that
- * would exceed it fails with MLCT_ENOMEM before enqueuing any work. */
+ * would exceed it fails with MLCT_ENOMEM before enqueuing any work.  A cap below
+ * what is held gives back the slot that only makes calls faster. */
 mlct_status mlct_set_workspace_limit(mlct_ctx* ctx, uint64_t bytes);
 
 /* Context options.  MLCT_OPT_TWO_STEP (default 0): 1 runs two recurrence steps

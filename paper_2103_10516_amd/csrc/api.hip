@@ -82,6 +82,18 @@ mlct_status ws_drop(mlct_ctx* ctx, int slot) {
   return MLCT_OK;
 }
 
+// Device memory; where there is none left, the spare slot gives its own back
+// first.
+bool dev_malloc(mlct_ctx* ctx, void** p, size_t bytes) {
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    if (!ctx->slots[WS_SPARE].ptr || ws_drop(ctx, WS_SPARE) != MLCT_OK) return false;
+  }
+  return false;
+}
+
 // Grow-only workspace slot.  Growing frees the old buffer (hipFree waits for
 // the device), so pointers from an earlier ws_get of the same slot become
 // invalid; callers take all slots they need before enqueuing work.
@@ -92,9 +104,9 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
     *out = b.ptr;
     return MLCT_OK;
   }
-  // packed dense operands are a spare: they give way to what a call needs
-  if (slot != WS_DPACK && ctx->ws_limit && ctx->ws_total - b.bytes + bytes > ctx->ws_limit)
-    CHECK(ws_drop(ctx, WS_DPACK));
+  // the spare gives way to what a call needs
+  if (slot != WS_SPARE && ctx->ws_limit && ctx->ws_total - b.bytes + bytes > ctx->ws_limit)
+    CHECK(ws_drop(ctx, WS_SPARE));
   const uint64_t new_total = ctx->ws_total - b.bytes + bytes;
   if (ctx->ws_limit && new_total > ctx->ws_limit)
     return fail(ctx, MLCT_ENOMEM, "workspace of %llu bytes exceeds the limit of %llu",
@@ -103,7 +115,7 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
   // so a run of calls on ever larger operators reallocates a few times
   // rather than on every call; never past the limit
   size_t want = bytes;
-  if (b.bytes) {
+  if (b.bytes && slot != WS_SPARE) {
     want = std::max(bytes, b.bytes + b.bytes / 2);
     want = (want + ((size_t)1 << 21) - 1) & ~(((size_t)1 << 21) - 1);
     if (ctx->ws_limit && ctx->ws_total - b.bytes + want > ctx->ws_limit) want = bytes;
@@ -116,14 +128,9 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
     b.bytes = 0;
   }
   void* p = nullptr;
-  if (hipMalloc(&p, want) != hipSuccess) {
-    (void)hipGetLastError();
-    const bool spare = slot != WS_DPACK && ctx->slots[WS_DPACK].ptr;
-    if (spare) CHECK(ws_drop(ctx, WS_DPACK));
-    if ((want == bytes && !spare) || hipMalloc(&p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
+  if (!dev_malloc(ctx, &p, want)) {
+    if (want == bytes || !dev_malloc(ctx, &p, bytes))
       return fail(ctx, MLCT_ENOMEM, "hipMalloc(%zu) failed", bytes);
-    }
     want = bytes;
   }
   b.ptr = p;
@@ -665,10 +672,8 @@ mlct_status build_hubs(mlct_ctx* ctx, mlct::CsrMat& mat, void** mem_out) {
   const size_t nch = cs.size();
   const size_t words = (size_t)n + (n + 1) + 3 * nch;
   void* mem = nullptr;
-  if (hipMalloc(&mem, words * sizeof(int32_t)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (!dev_malloc(ctx, &mem, words * sizeof(int32_t)))
     return fail(ctx, MLCT_ENOMEM, "no memory for the hub table");
-  }
   std::vector<int32_t> all;
   all.reserve(words);
   all.insert(all.end(), rows.begin(), rows.end());
@@ -735,8 +740,7 @@ mlct_status dense_operand(mlct_ctx* ctx, const mlct_op* cop, int prec, const voi
   if (prec == MLCT_BF16X3) {
     if (!op->split_hi) {
       void *hi = nullptr, *lo = nullptr;
-      if (hipMalloc(&hi, (size_t)d * d * 2) != hipSuccess || hipMalloc(&lo, (size_t)d * d * 2) != hipSuccess) {
-        (void)hipGetLastError();
+      if (!dev_malloc(ctx, &hi, (size_t)d * d * 2) || !dev_malloc(ctx, &lo, (size_t)d * d * 2)) {
         if (hi) (void)hipFree(hi);
         return fail(ctx, MLCT_ENOMEM, "no memory for the bf16 split of A");
       }
@@ -751,10 +755,8 @@ mlct_status dense_operand(mlct_ctx* ctx, const mlct_op* cop, int prec, const voi
   void** slot = prec == MLCT_FP64 ? &op->a64 : &op->a32;
   if (!*slot) {
     void* p = nullptr;
-    if (hipMalloc(&p, (size_t)d * d * (prec == MLCT_FP64 ? 8 : 4)) != hipSuccess) {
-      (void)hipGetLastError();
+    if (!dev_malloc(ctx, &p, (size_t)d * d * (prec == MLCT_FP64 ? 8 : 4)))
       return fail(ctx, MLCT_ENOMEM, "no memory for a converted copy of A");
-    }
     HIPCHK(ctx, launch_dense_convert(ctx->stream, op->A, op->dtype, d, op->lda, p));
     *slot = p;
   }
@@ -771,8 +773,7 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
   if (!op->pack_hi) {
     const size_t bytes = dense_pack_bytes(MLCT_BF16X3, op->d, op->d);
     void *h = nullptr, *l = nullptr;
-    if (hipMalloc(&h, bytes) != hipSuccess || hipMalloc(&l, bytes) != hipSuccess) {
-      (void)hipGetLastError();
+    if (!dev_malloc(ctx, &h, bytes) || !dev_malloc(ctx, &l, bytes)) {
       if (h) (void)hipFree(h);
       return fail(ctx, MLCT_ENOMEM, "no memory for the packed bf16 split of A");
     }
@@ -786,7 +787,7 @@ mlct_status dense_packed_a(mlct_ctx* ctx, const mlct_op* cop, const void* hi, co
 }
 
 // The tile of a block of bpad probes with S steps, and whether it reads packed
-// operands, whose workspace (WS_DPACK) is taken here.  FP32 and FP64 pack
+// operands, whose workspace (WS_SPARE) is taken here.  FP32 and FP64 pack
 // matrix and probes anew for each block, which its steps have to pay for
 // (dense_pack_steps).  Where there is no memory for packed operands, the block
 // goes without.
@@ -831,7 +832,7 @@ mlct_status dense_shape(mlct_ctx* ctx, const mlct_op* op, int prec, int64_t lda,
       st = dense_packed_a(ctx, op, a0, a1, &a0, &a1);
     }
     void* w;
-    if (st == MLCT_OK) st = ws_get(ctx, WS_DPACK, prec == MLCT_BF16X3 ? 4 * pv : pa + 2 * pv, &w);
+    if (st == MLCT_OK) st = ws_get(ctx, WS_SPARE, prec == MLCT_BF16X3 ? 4 * pv : pa + 2 * pv, &w);
     if (st != MLCT_ENOMEM) return st;
     ctx->err.clear();
     *packed = false;
@@ -913,7 +914,7 @@ mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, doub
     const size_t pb = dense_pack_bytes(prec, bpad, d);
     void* w;
     if (prec == MLCT_BF16X3) {
-      CHECK(ws_get(ctx, WS_DPACK, 4 * pb, &w));
+      CHECK(ws_get(ctx, WS_SPARE, 4 * pb, &w));
       for (int i = 0; i < 4; ++i) vpk[i] = static_cast<char*>(w) + i * pb;
       CHECK(dense_packed_a(ctx, op, a0, a1, &pa_hi, &pa_lo));
       HIPCHK(ctx, launch_dense_pack_v(s, static_cast<const float*>(buf[0]), bpad, d, vpk[0],
@@ -921,7 +922,7 @@ mlct_status run_block_dense(mlct_ctx* ctx, const mlct_op* op, double alpha, doub
       HIPCHK(ctx, hipMemsetAsync(vpk[2], 0, 2 * pb, s));
     } else {
       const size_t pa = dense_pack_bytes(prec, d, d);
-      CHECK(ws_get(ctx, WS_DPACK, pa + 2 * pb, &w));
+      CHECK(ws_get(ctx, WS_SPARE, pa + 2 * pb, &w));
       vpk[0] = static_cast<char*>(w) + pa;
       vpk[2] = vpk[0] + pb;
       HIPCHK(ctx, launch_dense_pack_plain(s, prec, a0, lda, buf[0], bpad, d, w, vpk[0], vpk[2]));
@@ -1033,8 +1034,9 @@ mlct_status refresh_bands(mlct_ctx* ctx, mlct_op* op) {
       continue;
     }
     if (m->band && m->band_groups == p.ngroups) continue;
-    if (!op->band_mem)
-      HIPCHK(ctx, hipMalloc(&op->band_mem, 2 * (size_t)(kMaxBandGroups + 1) * sizeof(int32_t)));
+    if (!op->band_mem &&
+        !dev_malloc(ctx, &op->band_mem, 2 * (size_t)(kMaxBandGroups + 1) * sizeof(int32_t)))
+      return fail(ctx, MLCT_EDEVICE, "hipMalloc failed: no memory for the row bands");
     int32_t* band = static_cast<int32_t*>(op->band_mem) + k * (kMaxBandGroups + 1);
     HIPCHK(ctx, launch_csr_bands(ctx->stream, m->rowptr, m->nrows, p.ngroups, band));
     m->band = band;
@@ -1044,6 +1046,10 @@ mlct_status refresh_bands(mlct_ctx* ctx, mlct_op* op) {
 }
 
 }  // namespace
+
+// mlct_estimate_batch with its memory in workspace slot ``slot``.
+static mlct_status estimate_batch_in(mlct_ctx* ctx, int32_t nitems, const mlct_batch_item* items,
+                                     int32_t prec, int32_t mode, mlct_result* outs, int slot);
 
 // =========================================================================
 extern "C" {
@@ -1118,6 +1124,10 @@ mlct_status mlct_timing_read(const mlct_ctx* ctx, int32_t kernel, int64_t* launc
 mlct_status mlct_set_workspace_limit(mlct_ctx* ctx, uint64_t bytes) {
   if (!ctx) return MLCT_EINVAL;
   ctx->ws_limit = bytes;
+  if (bytes && ctx->ws_total > bytes && ctx->slots[WS_SPARE].ptr) {
+    CHECK(set_device(ctx));
+    return ws_drop(ctx, WS_SPARE);
+  }
   return MLCT_OK;
 }
 
@@ -1275,10 +1285,7 @@ mlct_status mlct_op_gram_csr(mlct_ctx* ctx, int64_t rows, int64_t cols, int64_t 
   }
   const size_t words = (size_t)(cols + 1) + nnz + (val_dev ? nnz : 0);
   void* mem = nullptr;
-  if (hipMalloc(&mem, words * 4) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(ctx, MLCT_ENOMEM, "no memory for X^T");
-  }
+  if (!dev_malloc(ctx, &mem, words * 4)) return fail(ctx, MLCT_ENOMEM, "no memory for X^T");
   int32_t* base = static_cast<int32_t*>(mem);
   hipError_t e1 = hipMemcpy(base, rpt.data(), (cols + 1) * 4, hipMemcpyHostToDevice);
   if (e1 == hipSuccess && nnz > 0) e1 = hipMemcpy(base + cols + 1, clt.data(), nnz * 4, hipMemcpyHostToDevice);
@@ -1491,7 +1498,8 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
   // one length) 272 -> 163, 371 -> 206.  Past the lines: 22,500 rows 8:128,40:64
   // 383 -> 370, 35,937 rows 1,840 -> 2,015; graph of 40,000 10:128,30:128,60:64
   // 2,028 -> 1,950, of 50,000 2,055 -> 2,200.  These two take the shared
-  // launches' memory only where it is small, and do without when there is none.
+  // launches' memory only where it is small, from the spare, and do without
+  // when there is none.
   if (op->kind == OP_CSR && prec == MLCT_FP32 && op->d < ctx->batch_solo_rows &&
       (uint64_t)op->d * 64 * 4 <= 0xFFFFFFFFull &&
       plan_csr(op->d, op->tuned_groups).ngroups < kSmallGroups) {
@@ -1516,7 +1524,7 @@ mlct_status mlct_estimate(mlct_ctx* ctx, const mlct_op* op, mlct_func f, double 
     if (usual) return mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, out);
     if (small) {
       mlct_result h;
-      const mlct_status st = mlct_estimate_batch(ctx, 1, &it, prec, mode_flags, &h);
+      const mlct_status st = estimate_batch_in(ctx, 1, &it, prec, mode_flags, &h, WS_SPARE);
       if (st == MLCT_ESPECTRUM) return outside(h.max_moment_ratio);
       if (st == MLCT_OK) *out = h;
       if (st != MLCT_ENOMEM) return st;
@@ -1646,11 +1654,9 @@ mlct_status mlct_op_gram(mlct_ctx* ctx, int64_t rows, int64_t cols, const void* 
   if (prec != MLCT_FP32) return fail(ctx, MLCT_EUNSUPPORTED, "the Gram matrix is formed in FP32");
   CHECK(set_device(ctx));
   void* G = nullptr;
-  if (hipMalloc(&G, (size_t)cols * cols * sizeof(float)) != hipSuccess) {
-    (void)hipGetLastError();
+  if (!dev_malloc(ctx, &G, (size_t)cols * cols * sizeof(float)))
     return fail(ctx, MLCT_ENOMEM, "no memory for the %lld x %lld Gram matrix", (long long)cols,
                 (long long)cols);
-  }
   {
     LaunchTimer tm(ctx, MLCT_KERNEL_GRAM);
     hipError_t e = launch_gram(ctx->stream, static_cast<const float*>(X_dev), rows, cols, ldx,
@@ -1774,26 +1780,33 @@ mlct_status mlct_triangles(mlct_ctx* ctx, const mlct_op* op, int64_t m, uint64_t
   const int64_t ybytes = op->d * kBlockProbes * (int64_t)sizeof(int16_t);
   int panels = (int)std::min<int64_t>(kTriPanels, (m + kBlockProbes - 1) / kBlockProbes);
   panels = (int)std::max<int64_t>(1, std::min<int64_t>(panels, kMaxY / ybytes));
+  // One panel lies in the slots of the recurrence's vectors; more lie in the
+  // spare, taken last, so that other calls' needs come before them.
+  const size_t zbytes = (size_t)op->d * sizeof(uint64_t);
+  const size_t sbytes = op->csr.max_row_nnz > 32767
+                            ? (size_t)op->csr.hub_n * kBlockProbes * sizeof(int32_t)
+                            : 0;
   void *z, *y, *part, *w, *res, *side = nullptr;
-  auto take = [&](int np) -> mlct_status {
-    CHECK(ws_get(ctx, WS_V0, (size_t)op->d * np * sizeof(uint64_t), &z));  // packed signs
-    CHECK(ws_get(ctx, WS_V1, (size_t)np * ybytes, &y));
-    if (op->csr.max_row_nnz > 32767)
-      CHECK(ws_get(ctx, WS_TRISIDE, (size_t)np * op->csr.hub_n * kBlockProbes * sizeof(int32_t),
-                   &side));
-    CHECK(ws_get(ctx, WS_PART, (size_t)plan.ngroups * sizeof(uint64_t), &part));
-    CHECK(ws_get(ctx, WS_TRI, (size_t)m * 3 * sizeof(long long), &w));
-    return ws_get(ctx, WS_RESULT, sizeof(mlct_tri_result), &res);
-  };
-  mlct_status got = take(panels);
-  if (got == MLCT_ENOMEM && panels > 1) {
-    // what the wide attempt took goes back before the narrow one
-    ctx->err.clear();
-    for (int slot : {WS_V0, WS_V1, WS_TRISIDE}) CHECK(ws_drop(ctx, slot));
-    panels = 1;
-    got = take(1);
+  CHECK(ws_get(ctx, WS_PART, (size_t)plan.ngroups * sizeof(uint64_t), &part));
+  CHECK(ws_get(ctx, WS_TRI, (size_t)m * 3 * sizeof(long long), &w));
+  CHECK(ws_get(ctx, WS_RESULT, sizeof(mlct_tri_result), &res));
+  if (panels > 1) {
+    const mlct_status st = ws_get(ctx, WS_SPARE, panels * (ybytes + zbytes + sbytes), &y);
+    if (st == MLCT_OK) {  // (ybytes is a multiple of 128, zbytes of 8)
+      z = static_cast<char*>(y) + panels * ybytes;
+      side = static_cast<char*>(z) + panels * zbytes;
+    } else if (st == MLCT_ENOMEM) {
+      ctx->err.clear();
+      panels = 1;
+    } else {
+      return st;
+    }
   }
-  CHECK(got);
+  if (panels == 1) {
+    CHECK(ws_get(ctx, WS_V0, zbytes, &z));  // packed signs
+    CHECK(ws_get(ctx, WS_V1, ybytes, &y));
+    if (sbytes) CHECK(ws_get(ctx, WS_TRISIDE, sbytes, &side));
+  }
   hipStream_t s = ctx->stream;
   long long* W = static_cast<long long*>(w);
   uint64_t* Z = static_cast<uint64_t*>(z);
@@ -1863,11 +1876,7 @@ void mlp_free(mlct_mlp* m) {
 }
 
 mlct_status mlp_malloc(mlct_ctx* ctx, void** p, size_t bytes) {
-  if (hipMalloc(p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    *p = nullptr;
-    return fail(ctx, MLCT_ENOMEM, "hipMalloc(%zu) failed", bytes);
-  }
+  if (!dev_malloc(ctx, p, bytes)) return fail(ctx, MLCT_ENOMEM, "hipMalloc(%zu) failed", bytes);
   return MLCT_OK;
 }
 
@@ -2292,10 +2301,8 @@ struct HostBlock {
 
 }  // namespace
 
-extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
-                                           const mlct_batch_item* items, int32_t prec,
-                                           int32_t mode, mlct_result* outs) {
-  if (!ctx) return MLCT_EINVAL;
+static mlct_status estimate_batch_in(mlct_ctx* ctx, int32_t nitems, const mlct_batch_item* items,
+                                     int32_t prec, int32_t mode, mlct_result* outs, int slot) {
   ctx->err.clear();
   if (nitems < 1 || !items || !outs) return fail(ctx, MLCT_EINVAL, "need items and outs");
   const int interp = (mode & MLCT_LEVEL_INTERP) ? 1 : 0;
@@ -2448,7 +2455,7 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
   bytes += align8((size_t)variants.size() * (max_steps + 1) * 8 * sizeof(int64_t)) +
            align8((nb + 1) * sizeof(int32_t)) + 64;
   void* ws;
-  CHECK(ws_get(ctx, WS_BATCH, bytes, &ws));
+  CHECK(ws_get(ctx, slot, bytes, &ws));
   Carver cv{static_cast<char*>(ws)};
   // the tables first, in one piece: one copy brings them over
   BatchBlock* dtab = cv.take<BatchBlock>(nb);
@@ -2737,6 +2744,13 @@ extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
   }
   if (escaped) return fail(ctx, MLCT_ESPECTRUM, "an item's spectrum is not inside its [a, b]");
   return MLCT_OK;
+}
+
+extern "C" mlct_status mlct_estimate_batch(mlct_ctx* ctx, int32_t nitems,
+                                           const mlct_batch_item* items, int32_t prec,
+                                           int32_t mode, mlct_result* outs) {
+  if (!ctx) return MLCT_EINVAL;
+  return estimate_batch_in(ctx, nitems, items, prec, mode, outs, WS_BATCH);
 }
 
 // Autotuner for batches: times the two launch forms on the caller's batch

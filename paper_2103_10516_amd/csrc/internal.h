@@ -171,11 +171,14 @@ struct mlct_mlp {
 
 namespace mlct {
 
-// Workspace slot indices (each slot grows independently).
+// Workspace slot indices (each slot grows independently).  WS_SPARE holds what
+// only makes a call faster (packed dense operands, further triangle panels, the
+// shared launches of small estimates): one of them at a time, taken after all
+// else that the call needs, given up whenever any slot needs the room.
 enum Slot {
   WS_V0 = 0, WS_V1, WS_PART, WS_MU, WS_COEF, WS_QSTAT, WS_RESULT, WS_MISC,
   WS_TRI, WS_LANCZOS, WS_DENSE, WS_MLP, WS_MU2, WS_BATCH, WS_HUB, WS_PLAN, WS_STATS, WS_GRAMW, WS_SLQ, WS_SLQQ,
-  WS_DPACK, WS_CBW, WS_FSYNC, WS_FABORT, WS_TRISIDE, WS_NSLOTS
+  WS_SPARE, WS_CBW, WS_FSYNC, WS_FABORT, WS_TRISIDE, WS_NSLOTS
 };
 
 // ---- probe-generation constants (SplitMix64) ------------------------------
