@@ -568,7 +568,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(
   const int mt = L % mtiles, nt = L / mtiles;
   const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * (16 * TN);
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Uniform, but for row-major operands of 32 probes, whose loads then get
+  // slower (step at d = 20,000: FP32 666 -> 700 us, FP64 1,250 -> 1,294; of 64
+  // probes 1,170 -> 1,130, 1,950 -> 1,760).
+  const int wave = PK || TM == 4 ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                                 : (int)(threadIdx.x >> 6);
   const int g = lane >> 4, rl = lane & 15;
 
   // Rows past d read row 0: column n of the product depends on row n of A
