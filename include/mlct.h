@@ -495,7 +495,9 @@ mlct_status mlct_estimate_auto(mlct_ctx* ctx, const mlct_op* op, mlct_func f, do
  * there, keyed by the operator's shape (dense: and by precision and block
  * width); CSR operators of the same shape pick it up when they are created,
  * dense operators whenever a block of that precision and width runs.
- * Values in the file that the autotuner could not have chosen are ignored.
+ * Values in the file that the autotuner could not have chosen are ignored, and
+ * so are dense decisions without the word "packed", which were taken between
+ * other kernels.
  * choice_out (may be NULL): the value kept. */
 mlct_status mlct_autotune(mlct_ctx* ctx, mlct_op* op, int32_t B_max, int32_t prec,
                           int32_t* choice_out);

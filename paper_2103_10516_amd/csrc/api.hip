@@ -213,8 +213,8 @@ std::string tune_key(const mlct_op* op, int prec, int64_t bpad) {
     snprintf(buf, sizeof buf, "%s d=%lld nnz=%lld maxrow=%d pattern=%d",
              op->kind == OP_CSR ? "csr" : "gramcsr", (long long)op->d, (long long)op->csr.nnz,
              op->csr.max_row_nnz, op->csr.val == nullptr ? 1 : 0);
-  else
-    snprintf(buf, sizeof buf, "dense d=%lld prec=%d bpad=%lld", (long long)op->d, prec,
+  else  // ("packed": decisions taken before choice 3 was the packed kernel lack it)
+    snprintf(buf, sizeof buf, "dense d=%lld prec=%d bpad=%lld packed", (long long)op->d, prec,
              (long long)bpad);
   return buf;
 }
@@ -3185,7 +3185,9 @@ extern "C" mlct_status mlct_autotune(mlct_ctx* ctx, mlct_op* op, int32_t B_max, 
   if (csr) prec = MLCT_FP32;
   CHECK(check_mode_prec(ctx, MLCT_DIRECT, prec));
   const int64_t block = csr ? kBlockProbes : std::max<int64_t>(32, std::min<int64_t>(B_max, kDenseMaxBlock));
-  const int degree = 8;
+  // steps of a timed block (direct form): a dense block pays for packing once,
+  // so it is timed at a length that programs use
+  const int degree = csr ? 8 : 32;
   std::vector<int> cands;
   if (csr) cands = kCsrGroupCands;
   else cands = kDenseTileCands;
