@@ -798,18 +798,21 @@ hipError_t launch_tri_pass2(hipStream_t s, const CsrMat& m, const CsrStepPlan& p
   auto go = [&](auto pw, int u0, int units) {
     constexpr int PW = decltype(pw)::value;
     const dim3 grid(plan.ngroups, units);
-    const bool off32 = (uint64_t)m.ncols * PW * kPanel * sizeof(int16_t) <= 0xFFFFFFFFull;
 #define MLCT_TRI2(C, O)                                                                  \
   tri_pass2_kernel<PW, C, O><<<grid, kThreads2, 0, s>>>(                                 \
       m.rowptr, m.col, m.nrows, zbits, y, hs, hub_rows(m), banded(m, plan), asym, escapes, \
       panels, u0, active, reinterpret_cast<unsigned long long*>(w))
-    if (m.max_row_nnz > 32767) {
-      if (off32) MLCT_TRI2(true, true);
-      else MLCT_TRI2(true, false);
-    } else {
-      if (off32) MLCT_TRI2(false, true);
-      else MLCT_TRI2(false, false);
+    // (further panels are taken only while all of y stays within 1 GiB, so that
+    // two of them always have 32-bit offsets)
+    if constexpr (PW == 1) {
+      if ((uint64_t)m.ncols * kPanel * sizeof(int16_t) > 0xFFFFFFFFull) {
+        if (m.max_row_nnz > 32767) MLCT_TRI2(true, false);
+        else MLCT_TRI2(false, false);
+        return;
+      }
     }
+    if (m.max_row_nnz > 32767) MLCT_TRI2(true, true);
+    else MLCT_TRI2(false, true);
 #undef MLCT_TRI2
   };
   if (panels >= 2) go(std::integral_constant<int, 2>(), 0, panels / 2);
