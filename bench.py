@@ -857,6 +857,25 @@ def extra_slq(mlct, dev):
     return out
 
 
+def brief(x):
+    """A secondary measurement as the result line holds it: numbers to five
+    digits, without descriptions, tables of records and long lists."""
+    def kept(v):
+        if isinstance(v, str):
+            return len(v) <= 40
+        return not isinstance(v, (list, tuple)) or (
+            len(v) <= 8 and not any(isinstance(e, dict) for e in v))
+
+    if isinstance(x, dict):
+        return {k: brief(v) for k, v in x.items() if kept(v)}
+    if isinstance(x, (list, tuple)):
+        return [brief(e) for e in x]
+    if isinstance(x, (float, np.floating)):
+        v = float(f"{x:.5g}")
+        return int(v) if v.is_integer() and abs(v) < 1e15 else v
+    return x
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__.split("\n\n")[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -988,8 +1007,10 @@ def main():
         except Exception as exc:  # a failed extra must not lose the headline number
             traceback.print_exc()
             secondary[name] = {"error": repr(exc)}
+        # in full here: the result line has to stay short enough to be read back
+        print(f"# detail {name}: {json.dumps(secondary[name])}", file=sys.stderr, flush=True)
     if secondary:
-        out["secondary"] = secondary
+        out["secondary"] = brief(secondary)
     if not args.no_cpu_baseline:
         print("# cpu baseline (oracle) ...", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(g, w["a"], w["b"], 99)
