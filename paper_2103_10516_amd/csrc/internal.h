@@ -15,7 +15,8 @@ namespace mlct {
 // Width of a probe block in the CSR recurrence: one probe per wavefront lane.
 constexpr int kBlockProbes = 64;
 // CSR rows with more entries than kHubLen are reduced in chunks of at most
-// kHubChunk entries by a separate launch before each step.
+// kHubChunk entries, shared by the workgroup of their band (the Lanczos product:
+// by a launch of its own before each product).
 constexpr int kHubLen = 256;
 constexpr int kHubChunk = 256;
 
@@ -442,8 +443,10 @@ hipError_t launch_slq_combine(hipStream_t s, const double* mu, int64_t ldmu, con
 // Groups of up to kTriPanels panels of 64 probes.  launch_tri_init: z, one
 // 64-bit sign word per row and panel, a row's panels side by side.
 // launch_tri_sym: *asym = 0 if the pattern is symmetric (part: ngroups words of
-// scratch).  Pass 1: y = A z (int16, [panel][d][64]; values past +-32767 as
-// -32768 with the exact value in side[panel][hub slot][64], needed with rows
+// scratch).  Pass 1: y = A z (int16; panels 2u and 2u + 1 side by side in rows
+// of 128 from u * 2 d * 64 on, a last odd panel in rows of 64, a panel's probes
+// in the order of probe_at; values past +-32767 as -32768 with the exact value
+// in side[panel][hub slot][64], probes in y's order, needed with rows
 // longer than 32,767 only; *escapes, cleared by launch_tri_init, gets the bit
 // of each panel that has one); pass 2 adds w1, w2, w3 of the group's first
 // `active` probes to w (3 per probe).
