@@ -113,9 +113,9 @@ mlct_status ws_get(mlct_ctx* ctx, int slot, size_t bytes, void** out) {
                 (unsigned long long)new_total, (unsigned long long)ctx->ws_limit);
   // a slot that grows again grows by at least half its size (2 MiB granules),
   // so a run of calls on ever larger operators reallocates a few times
-  // rather than on every call; never past the limit
+  // rather than on every call; never past the limit (the spare: below 1 GiB)
   size_t want = bytes;
-  if (b.bytes && slot != WS_SPARE) {
+  if (b.bytes && (slot != WS_SPARE || bytes < (size_t)1 << 30)) {
     want = std::max(bytes, b.bytes + b.bytes / 2);
     want = (want + ((size_t)1 << 21) - 1) & ~(((size_t)1 << 21) - 1);
     if (ctx->ws_limit && ctx->ws_total - b.bytes + want > ctx->ws_limit) want = bytes;
